@@ -26,6 +26,7 @@
 // when read (k_link_finish).
 #include "engine.hpp"
 #include "kernels.hpp"
+#include "params.hpp"
 
 namespace lbe {
 
@@ -732,59 +733,6 @@ k_adjoint_out(const T* __restrict__ lam, const uint32_t* __restrict__ info,
 
 // ----------------------------------------------------------------------------
 
-template <class L, class T>
-static Params<L, T> adj_params(const Engine& e) {
-    Params<L, T> p;
-    for (int k = 0; k < L::Q; ++k)
-        p.rate[k] = (T)(L::conserved(k) ? 0.0 : e.s[k] / (double)TAB<L>.norm[k]);
-    for (int a = 0; a < 3; ++a) p.G[a] = (T)(3.0 * e.rho0 * (a < L::D ? e.g[a] : 0.0));
-    p.drho = (T)(e.xbc == XBC_PRESSURE ? e.drho : 0.0);
-    for (int i = 0; i < L::Q; ++i) {
-        double eg = 0;
-        for (int a = 0; a < L::D; ++a) eg += L::E[i][a] * e.g[a];
-        p.force[i] = (T)(3.0 * L::W[i] * e.rho0 * eg);
-        p.seam[i] = (T)(L::W[i] * (e.xbc == XBC_PRESSURE ? e.drho : 0.0));
-    }
-    p.rho0 = (T)e.rho0;
-    p.inv_rho0 = (T)(1.0 / e.rho0);
-    p.c0 = 1.0 - e.b;
-    p.rho0_d = e.rho0;
-    p.wall_scale = e.wall_decay == 1.0 ? 1.0 : e.wall_scale;
-    p.c1d = e.two_node ? e.d_lkc1d : nullptr;
-    return p;
-}
-
-static Grid adj_grid(const Engine& e) {
-    Grid g;
-    g.nx = (uint32_t)e.nx;
-    g.ny = (uint32_t)e.ny;
-    g.nz = (uint32_t)e.nz;
-    g.N = (uint32_t)e.N;
-    g.S = (uint32_t)e.S;
-    // the adjoint kernels index waves and links, not blocks of a node launch
-    g.nblocks = (uint32_t)((e.N + BX - 1) / BX);
-    g.bpr = 0u;
-    return g;
-}
-
-template <class F>
-static hipError_t adj_dispatch(const Engine& e, F&& f) {
-    auto by_xbc = [&](auto lat, auto prec) -> hipError_t {
-        using L = decltype(lat);
-        using T = decltype(prec);
-        switch (e.xbc) {
-            case XBC_PRESSURE: return f(L{}, T{}, std::integral_constant<int, XBC_PRESSURE>{});
-            case XBC_OUTFLOW: return f(L{}, T{}, std::integral_constant<int, XBC_OUTFLOW>{});
-            default: return f(L{}, T{}, std::integral_constant<int, XBC_PERIODIC>{});
-        }
-    };
-    if (e.lattice == 0)
-        return e.precision == 0 ? by_xbc(D2Q9{}, double{}) : by_xbc(D2Q9{}, float{});
-    if (e.lattice == 2)
-        return e.precision == 0 ? by_xbc(D3Q15{}, double{}) : by_xbc(D3Q15{}, float{});
-    return e.precision == 0 ? by_xbc(D3Q19{}, double{}) : by_xbc(D3Q19{}, float{});
-}
-
 static uint32_t wave_blocks(int64_t waves) { return (uint32_t)((waves + BX / 64 - 1) / (BX / 64)); }
 
 int64_t adjoint_blocks(const Engine& e) {
@@ -794,7 +742,7 @@ int64_t adjoint_blocks(const Engine& e) {
 hipError_t launch_adjoint_step(Engine& e, const Snapshot* fwd, const Snapshot* next,
                                const void* rec, const void* lam_in, void* lam_out,
                                const AdjointObjective& obj) {
-    const Grid g = adj_grid(e);
+    const Grid g = make_grid(e);
     const uint32_t wpr = e.nx % 64 == 0 ? (uint32_t)(e.nx / 64) : 0u;
     const WaveList waves{e.d_wact, (uint32_t)e.n_wact, wpr};
     AdjArgs a;
@@ -807,7 +755,7 @@ hipError_t launch_adjoint_step(Engine& e, const Snapshot* fwd, const Snapshot* n
     a.x_out = obj.x_out;
     a.a_in = obj.kind == 3 ? obj.weight * obj.a_in / 3.0 : 0.0;
     a.a_out = obj.kind == 3 ? obj.weight * obj.a_out / 3.0 : 0.0;
-    return adj_dispatch(e, [&](auto lat, auto prec, auto xb) -> hipError_t {
+    return dispatch(e, [&](auto lat, auto prec, auto xb) -> hipError_t {
         using L = decltype(lat);
         using T = decltype(prec);
         constexpr int XB = decltype(xb)::value;
@@ -819,7 +767,7 @@ hipError_t launch_adjoint_step(Engine& e, const Snapshot* fwd, const Snapshot* n
                                      : k_adjoint<L, T, XB, false, false, true>)
                               : (wpr ? k_adjoint<L, T, XB, false, true, false>
                                      : k_adjoint<L, T, XB, false, false, false>);
-        const Params<L, T> prm = adj_params<L, T>(e);
+        const Params<L, T> prm = make_params<L, T>(e);
         const StepRecord<T> r = um ? record_at<T>(e, rec) : StepRecord<T>{};
         const size_t L1 = (size_t)std::max<int64_t>(e.n_links, 1);
         if (um && !e.ak_buf) return hipErrorInvalidValue;
@@ -888,7 +836,7 @@ hipError_t launch_link_gradients(Engine& e, double* dq, double* dphi) {
 hipError_t launch_two_node_adjoint(Engine& e, const Snapshot* next, const void* fib_next,
                                    void* lam_in, const AdjointObjective& obj) {
     if (e.n_links == 0) return hipSuccess;
-    const Grid g = adj_grid(e);
+    const Grid g = make_grid(e);
     AdjArgs a;
     a.obj_kind = obj.kind;
     a.obj_tag = obj.tag;
@@ -908,7 +856,7 @@ hipError_t launch_two_node_adjoint(Engine& e, const Snapshot* next, const void* 
     }
     double* gq = store ? e.tq_buf + (size_t)e.ak_pending * (size_t)std::max<int64_t>(e.n_links, 1)
                        : e.d_gq;
-    return adj_dispatch(e, [&](auto lat, auto prec, auto xb) -> hipError_t {
+    return dispatch(e, [&](auto lat, auto prec, auto xb) -> hipError_t {
         using L = decltype(lat);
         using T = decltype(prec);
         constexpr int XB = decltype(xb)::value;
@@ -916,29 +864,29 @@ hipError_t launch_two_node_adjoint(Engine& e, const Snapshot* next, const void* 
                            next ? (const T*)next->f : nullptr, (const T*)fib_next,
                            (T*)lam_in, e.d_lknode, e.d_lkdir, e.d_lktag,
                            e.d_lkc1d, e.d_lkd1d, gq, store ? 1 : 0, (uint32_t)e.n_links, g,
-                           adj_params<L, T>(e), a);
+                           make_params<L, T>(e), a);
         return hipGetLastError();
     });
 }
 
 hipError_t launch_link_pull(Engine& e, const Snapshot& s, void* out) {
     if (e.n_links == 0) return hipSuccess;
-    const Grid g = adj_grid(e);
+    const Grid g = make_grid(e);
     const unsigned nb = (unsigned)((e.n_links + BX - 1) / BX);
-    return adj_dispatch(e, [&](auto lat, auto prec, auto xb) -> hipError_t {
+    return dispatch(e, [&](auto lat, auto prec, auto xb) -> hipError_t {
         using L = decltype(lat);
         using T = decltype(prec);
         constexpr int XB = decltype(xb)::value;
         hipLaunchKernelGGL((k_link_pull<L, T, XB>), dim3(nb), dim3(BX), 0, e.stream,
                            (const T*)s.f, e.d_lknode, e.d_lkdir, (uint32_t)e.n_links, g,
-                           adj_params<L, T>(e), (T*)out);
+                           make_params<L, T>(e), (T*)out);
         return hipGetLastError();
     });
 }
 
 hipError_t launch_adjoint_out(Engine& e, const void* lam, double* out) {
     const unsigned nb = (unsigned)((e.N + BX - 1) / BX);
-    return adj_dispatch(e, [&](auto lat, auto prec, auto) -> hipError_t {
+    return dispatch(e, [&](auto lat, auto prec, auto) -> hipError_t {
         using L = decltype(lat);
         using T = decltype(prec);
         hipLaunchKernelGGL((k_adjoint_out<L, T>), dim3(nb), dim3(BX), 0, e.stream,

@@ -363,6 +363,79 @@ int forward_step(lbm_t* h, const Snapshot& in, const Snapshot& out, bool accumul
     return LBM_OK;
 }
 
+// Tiles for launches of several steps: the best plan whose regions hold their
+// links, none where single steps are expected to be as fast.
+int set_tiles(lbm_t* h, const int (*vel)[3]) {
+    Engine& e = h->e;
+    const int64_t n[3] = {e.nx, e.ny, e.nz};
+    const lbe::TileLimits lim = lbe::tile_limits(e);
+    lbe::TileLinks links;
+    e.tiles = lbe::TilePlan{};
+    for (const lbe::TilePlan& p : lbe::tile_plans(n, lim, e.Q, e.D, (int)e.elem))
+        if (lbe::tile_links(p, n, lim, e.Q, vel, e.lk_node_h, e.lk_dir_h, e.ibar_is_link,
+                            e.xbc == LBM_X_PRESSURE, e.xbc == LBM_X_OUTFLOW, links)) {
+            e.tiles = p;
+            break;
+        }
+    if (!e.tiles.halo) return LBM_OK;
+    static_assert(sizeof(lbe::TileLink) == sizeof(uint4), "device layout");
+    int rc;
+    HIPCHK(h, lbe::tile_setup(e));
+    if ((rc = upload(h, e.d_tile_first, links.first.data(), links.first.size()))) return rc;
+    if ((rc = upload(h, e.d_tile_link, reinterpret_cast<const uint4*>(links.link.data()),
+                     links.link.size())))
+        return rc;
+    return sync(h);   // the uploads read `links`
+}
+
+// How many of the next `left` steps from time t one launch on tiles may take
+// (0 or 1: the single step).  The objectives summed per block in node order
+// (mean u_x, pressure drop) and, with Eq. (211), the drag need the single step
+// inside their window.
+int64_t tile_steps(const Engine& e, int64_t t, int64_t left, bool accumulate) {
+    if (e.tiles.halo == 0 || e.poison) return 0;
+    if (accumulate && e.obj_kind != LBM_OBJ_NONE &&
+        !(e.obj_kind == LBM_OBJ_FORCE_X && !e.two_node)) {
+        if (t >= e.obj_t0 && t < e.obj_t1) return 0;
+        if (t < e.obj_t0) left = std::min(left, e.obj_t0 - t);
+    }
+    // equal launches rather than full ones and a short rest
+    const int64_t launches = (left + e.tiles.halo - 1) / e.tiles.halo;
+    return launches > 0 ? (left + launches - 1) / launches : 0;
+}
+
+// m forward steps from time e.t in one launch on tiles, the state after step s
+// of the launch into *out[s] where given
+int forward_tiles(lbm_t* h, const Snapshot& in, const Snapshot* const* out, int64_t m,
+                  bool accumulate) {
+    Engine& e = h->e;
+    double ws[lbe::kTileSteps];
+    for (int64_t s = 0; s < m; ++s)
+        ws[s] = e.wall_decay == 1.0 ? 1.0 : std::pow(e.wall_decay, (double)(e.t + s));
+    lbe::TileDrag drag;
+    if (accumulate && e.obj_kind == LBM_OBJ_FORCE_X && e.n_links) {
+        const int64_t s0 = std::max<int64_t>(e.obj_t0 - e.t, 0);
+        const int64_t s1 = std::min<int64_t>(e.obj_t1 - e.t, m);
+        if (s0 < s1) {
+            drag.acc = e.d_obj_acc;
+            drag.tag = e.obj_tag;
+            drag.s0 = (int)s0;
+            drag.s1 = (int)s1;
+            drag.weight = 1.0 / (double)(e.obj_t1 - e.obj_t0);
+        }
+    }
+    HIPCHK(h, lbe::launch_tile_steps(e, in, out, (int)m, ws, drag));
+    return LBM_OK;
+}
+
+// the same with only the last state kept
+int forward_tiles_last(lbm_t* h, const Snapshot& in, const Snapshot& last, int64_t m,
+                       bool accumulate) {
+    const Snapshot* out[lbe::kTileSteps] = {};
+    out[m - 1] = &last;
+    return forward_tiles(h, in, out, m, accumulate);
+}
+
 }  // namespace
 
 // =============================================================================
@@ -502,9 +575,18 @@ int adjoint_steps(lbm_t* h, int64_t n) {
                 }
             } else {
                 const int64_t nrep = j + 1 == nseg ? len : len - 1;
-                for (int64_t k = 0; k < nrep; ++k) {
-                    e.t = t_seg + k;   // forward_step reads e.t for the objective window and wall data
-                    if ((rc = forward_step(h, state(k), e.pool[k + 1], false))) break;
+                for (int64_t k = 0; k < nrep;) {
+                    e.t = t_seg + k;   // the steps read e.t for the wall data
+                    const int64_t m = tile_steps(e, e.t, nrep - k, false);
+                    if (m > 1) {
+                        const Snapshot* out[lbe::kTileSteps] = {};
+                        for (int64_t s = 0; s < m; ++s) out[s] = &e.pool[k + s + 1];
+                        if ((rc = forward_tiles(h, state(k), out, m, false))) break;
+                        k += m;
+                    } else {
+                        if ((rc = forward_step(h, state(k), e.pool[k + 1], false))) break;
+                        ++k;
+                    }
                 }
             }
             if (rc) break;
@@ -774,6 +856,7 @@ int lbm_set_geometry(lbm_t* h, const uint8_t* solid, int64_t n_links,
         }
         if ((rc = zero(h, b.wa, wa_bytes(e)))) return rc;
     }
+    if ((rc = set_tiles(h, E))) return rc;
     e.has_geometry = true;
     e.initialized = false;
     e.have_grad = false;
@@ -917,10 +1000,10 @@ int lbm_step(lbm_t* h, int64_t n) {
     if (!e.initialized) return fail(h, LBM_ESTATE, "initialise before stepping");
     if (e.timing && n > 0) HIPCHK(h, hipEventRecord(e.ev0, e.stream));
     int64_t left = n;
-    // small domains are launch-bound: replay captured loops of graph_steps
-    // steps while no objective window is open
+    // small domains without tiles are launch-bound: replay captured loops of
+    // graph_steps steps while no objective window is open
     const bool obj_open = e.obj_kind != LBM_OBJ_NONE && e.t < e.obj_t1 && e.t + n > e.obj_t0;
-    if (e.graph_steps > 0 && !obj_open && e.wall_decay == 1.0) {
+    if (e.graph_steps > 0 && e.tiles.halo == 0 && !obj_open && e.wall_decay == 1.0) {
         while (left >= e.graph_steps) {
             if (!e.graph_exec[e.cur]) {
                 const int rc = build_graph(h, e.cur);
@@ -932,11 +1015,15 @@ int lbm_step(lbm_t* h, int64_t n) {
             e.stepped = true;
         }
     }
-    for (; left > 0; --left) {
-        const int rc = forward_step(h, e.buf[e.cur], e.buf[e.cur ^ 1], true);
+    while (left > 0) {
+        const int64_t m = tile_steps(e, e.t, left, true);
+        const int64_t taken = std::max<int64_t>(m, 1);
+        const int rc = m > 1 ? forward_tiles_last(h, e.buf[e.cur], e.buf[e.cur ^ 1], m, true)
+                             : forward_step(h, e.buf[e.cur], e.buf[e.cur ^ 1], true);
         if (rc) return rc;
         e.cur ^= 1;
-        ++e.t;
+        e.t += taken;
+        left -= taken;
         e.stepped = true;
     }
     if (e.timing && n > 0) {
@@ -1107,7 +1194,7 @@ int lbm_set_objective(lbm_t* h, int kind, int32_t tag, int64_t t_begin, int64_t 
     e.obj_tag = tag;
     e.obj_t0 = t_begin;
     e.obj_t1 = t_end;
-    const int64_t len = kind == LBM_OBJ_FORCE_X ? lbe::link_blocks(e) : lbe::step_blocks(e);
+    const int64_t len = kind == LBM_OBJ_FORCE_X ? e.n_links : lbe::step_blocks(e);
     free_dev(e.d_obj_acc);
     e.obj_acc_len = 0;
     if (kind != LBM_OBJ_NONE) {
@@ -1160,9 +1247,13 @@ int lbm_objective(lbm_t* h, double* J) {
     Engine& e = h->e;
     *J = 0.0;
     if (e.obj_kind == LBM_OBJ_NONE || e.obj_acc_len == 0) return LBM_OK;
-    int rc = ensure_scratch(h, 1);
+    const bool links = e.obj_kind == LBM_OBJ_FORCE_X;
+    int rc = ensure_scratch(h, 1 + (links ? lbe::link_blocks(e) : 0));
     if (rc) return rc;
-    HIPCHK(h, lbe::launch_sum_blocks(e, e.d_obj_acc, e.obj_acc_len, 1, e.d_scratch));
+    if (links)
+        HIPCHK(h, lbe::launch_sum_links(e, e.d_obj_acc, e.d_scratch + 1, e.d_scratch));
+    else
+        HIPCHK(h, lbe::launch_sum_blocks(e, e.d_obj_acc, e.obj_acc_len, 1, e.d_scratch));
     HIPCHK(h, hipMemcpyAsync(J, e.d_scratch, 8, hipMemcpyDeviceToHost, e.stream));
     if ((rc = sync(h))) return rc;
     if (!std::isfinite(*J)) return fail(h, LBM_ENONFINITE, "objective is not finite");
@@ -1211,21 +1302,30 @@ int lbm_run_checkpointed(lbm_t* h, int64_t n, int64_t every) {
     // a checkpoint takes the current state's buffers (the state it must
     // keep) and hands its own, unused ones to the ping-pong pair: no copies
     drop_graphs(e);
-    for (int64_t s = 0; s < n; ++s) {
+    for (int64_t s = 0; s < n;) {
         int rc;
         const Snapshot* in = &e.buf[e.cur];
         if (nck && s % every == 0) {
             std::swap(e.ckpt[s / every], e.buf[e.cur]);
             in = &e.ckpt[s / every];
         }
-        const bool seg_end = (s + 1) % every == 0 || s + 1 == n;
-        void* rec = urec && seg_end ? e.rec_last[s / every] : nullptr;
-        if ((rc = forward_step(h, *in, e.buf[e.cur ^ 1], true, rec))) {
+        // the steps of the segment in launches on tiles, but a recorded last one
+        const int64_t seg_left = std::min((s / every + 1) * every, n) - s;
+        int64_t m = tile_steps(e, e.t, urec ? seg_left - 1 : seg_left, true);
+        if (m > 1) {
+            rc = forward_tiles_last(h, *in, e.buf[e.cur ^ 1], m, true);
+        } else {
+            m = 1;
+            void* rec = urec && seg_left == 1 ? e.rec_last[s / every] : nullptr;
+            rc = forward_step(h, *in, e.buf[e.cur ^ 1], true, rec);
+        }
+        if (rc) {
             e.run_t0 = -1;   // no sweep over a run that did not finish
             return rc;
         }
         e.cur ^= 1;
-        ++e.t;
+        e.t += m;
+        s += m;
         e.stepped = true;
     }
     // Eq. (211) on records: f_ibar(x_f, t) of every link at the final state,
@@ -1391,6 +1491,8 @@ int lbm_destroy(lbm_t* h) {
     free_dev(e.d_wave);
     free_dev(e.d_wact);
     free_dev(e.d_lkdir);
+    free_dev(e.d_tile_first);
+    free_dev(e.d_tile_link);
     free_dev(e.d_lknode);
     free_dev(e.d_perm);
     free_dev(e.d_lktag);

@@ -7,6 +7,8 @@
 #include <string>
 #include <vector>
 
+#include "tiling.hpp"
+
 namespace lbe {
 
 constexpr int kBlock = 256;             // threads per block of node launches
@@ -99,6 +101,10 @@ struct Engine {
     double* d_lkc1d = nullptr;          // c1 applied at the next pull (Eq. (211)), else 0
     double* d_lkd1d = nullptr;          // its gamma derivative
 
+    TilePlan tiles;                     // several steps per launch (halo 0: one)
+    uint32_t* d_tile_first = nullptr;   // the links of its regions (TileLinks)
+    uint4* d_tile_link = nullptr;
+
     // state: post-collision array A and link slots of the current time
     Snapshot buf[2];
     int cur = 0;
@@ -113,7 +119,7 @@ struct Engine {
     int64_t obj_x_in = 0, obj_x_out = -1;   // pressure-drop planes (-1: nx - 1)
     double obj_a_in = 0.0, obj_a_out = 0.0; // 1 / (fluid nodes of each plane)
     std::vector<int64_t> fluid_per_x;       // fluid nodes of each plane x = const
-    double* d_obj_acc = nullptr;        // per-block partial sums
+    double* d_obj_acc = nullptr;        // partial sums: per link (drag) or per block
     int64_t obj_acc_len = 0;
 
     // checkpointed run and adjoint
@@ -233,9 +239,11 @@ hipError_t launch_plane_density(Engine& e, const Snapshot& in, uint32_t x_in, ui
 // per-block partial momentum-exchange force: (nblocks, n_tags, D)
 hipError_t launch_force(Engine& e, const Snapshot& post, double* partials,
                         int64_t* nblocks);
-// accumulate the x force on one tag into per-block accumulators
+// acc[k] += weight times the x force on link k, for the links of one tag
 hipError_t launch_force_objective(Engine& e, const Snapshot& post, double* acc,
                                   int tag, double weight);
+// out[0] = sum of n values in a fixed order; partials: link_blocks(e) doubles
+hipError_t launch_sum_links(Engine& e, const double* v, double* partials, double* out);
 // LBM_DEBUG: fill n values of T (the handle's precision) at p with NaN
 hipError_t launch_fill_nan(Engine& e, void* p, size_t n);
 // out[c] = sum_b partials[b*cols + c], deterministic
@@ -247,6 +255,25 @@ hipError_t noalloc_scratch(int device, double** out);
 int64_t step_blocks(const Engine& e);       // logical blocks of a node launch
 int64_t adjoint_blocks(const Engine& e);    // blocks of the two adjoint launches together
 int64_t link_blocks(const Engine& e);       // blocks of a link launch
+
+// ---- launchers (tiles.hip) ----------------------------------------------------
+// What a block of a launch on tiles can hold for this handle.
+TileLimits tile_limits(const Engine& e);
+// once per plan, with the handle's device current
+hipError_t tile_setup(const Engine& e);
+// drag of the launch's steps s0 <= s < s1: weight times the x force on link k
+// is added to acc[k] for the links of one tag (acc null: none; not with
+// Eq. (211), whose link values the last step does not complete)
+struct TileDrag {
+    double* acc = nullptr;
+    int tag = 0, s0 = 0, s1 = 0;
+    double weight = 0.0;
+};
+// `steps` steps (at most e.tiles.halo) from `in`; out[s] receives the state
+// after step s or is null; the last is given.  ws: factor on the wall terms of
+// each step.
+hipError_t launch_tile_steps(Engine& e, const Snapshot& in, const Snapshot* const* out, int steps,
+                             const double* ws, const TileDrag& drag);
 
 // ---- launchers (adjoint.hip) -------------------------------------------------
 // One reverse step: lam_in = lambda(t+1) -> lam_out = lambda(t), with the

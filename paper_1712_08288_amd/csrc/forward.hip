@@ -14,6 +14,7 @@
 
 #include "engine.hpp"
 #include "kernels.hpp"
+#include "params.hpp"
 
 namespace lbe {
 
@@ -222,8 +223,8 @@ k_init(const double* __restrict__ df, const double* __restrict__ rho,
         T v = (T)f[i];
         if constexpr (XB == XBC_PRESSURE && L::E[i][0] != 0) {
             const int sg = seam_sign<L, i>(pos.ix, g.nx);
-            if (sg > 0) v -= seam_of<L, i, false>(p);
-            else if (sg < 0) v += seam_of<L, i, false>(p);
+            if (sg > 0) v = plus_seam<L, i, false, -1>(p, v);
+            else if (sg < 0) v = plus_seam<L, i, false, 1>(p, v);
         }
         A[pop_at<L::Q>(i, pl.template src<L, i>())] = v;
     });
@@ -423,8 +424,15 @@ k_force_obj(const T* __restrict__ B, const T* __restrict__ wa,
             }
         });
     }
-    const double s = block_sum(fx);
-    if (threadIdx.x == 0) acc[blockIdx.x] += weight * s;
+    if (fx != 0.0) acc[k] += weight * fx;
+}
+
+// per-block sums of n values
+__global__ void __launch_bounds__(BX)
+k_partial_sums(const double* __restrict__ v, uint32_t n, double* __restrict__ partials) {
+    const uint32_t k = blockIdx.x * BX + threadIdx.x;
+    const double s = block_sum(k < n ? v[k] : 0.0);
+    if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
 // NaN into n values (debug mode: slots a step leaves unwritten stay NaN)
@@ -450,18 +458,6 @@ k_sum_blocks(const double* __restrict__ partials, uint32_t rows, uint32_t cols,
 // ----------------------------------------------------------------------------
 // host side
 
-static Grid make_grid(const Engine& e) {
-    Grid g;
-    g.nx = (uint32_t)e.nx;
-    g.ny = (uint32_t)e.ny;
-    g.nz = (uint32_t)e.nz;
-    g.N = (uint32_t)e.N;
-    g.S = (uint32_t)e.S;
-    g.nblocks = (uint32_t)((e.N + BX - 1) / BX);
-    g.bpr = e.nx % BX == 0 ? (uint32_t)(e.nx / BX) : 0u;
-    return g;
-}
-
 unsigned launch_blocks(const Grid& g) { return g.nblocks; }
 
 int64_t step_blocks(const Engine& e) {
@@ -470,49 +466,6 @@ int64_t step_blocks(const Engine& e) {
 
 NodeMeta meta(const Engine& e) { return NodeMeta{e.d_info, e.d_wave}; }
 int64_t link_blocks(const Engine& e) { return (e.n_links + BX - 1) / BX; }
-
-template <class L, class T>
-static Params<L, T> make_params(const Engine& e) {
-    Params<L, T> p;
-    for (int k = 0; k < L::Q; ++k) {
-        const double r = L::conserved(k) ? 0.0 : e.s[k] / (double)TAB<L>.norm[k];
-        p.rate[k] = (T)r;
-    }
-    for (int a = 0; a < 3; ++a) p.G[a] = (T)(3.0 * e.rho0 * (a < L::D ? e.g[a] : 0.0));
-    p.drho = (T)(e.xbc == XBC_PRESSURE ? e.drho : 0.0);
-    for (int i = 0; i < L::Q; ++i) {
-        double eg = 0;
-        for (int a = 0; a < L::D; ++a) eg += L::E[i][a] * e.g[a];
-        p.force[i] = (T)(3.0 * L::W[i] * e.rho0 * eg);
-        p.seam[i] = (T)(L::W[i] * (e.xbc == XBC_PRESSURE ? e.drho : 0.0));
-    }
-    p.rho0 = (T)e.rho0;
-    p.inv_rho0 = (T)(1.0 / e.rho0);
-    p.c0 = 1.0 - e.b;
-    p.rho0_d = e.rho0;
-    p.wall_scale = e.wall_decay == 1.0 ? 1.0 : e.wall_scale;
-    p.c1d = e.two_node ? e.d_lkc1d : nullptr;
-    return p;
-}
-
-// runtime -> compile-time dispatch over lattice, precision and x boundary
-template <class F>
-static hipError_t dispatch(const Engine& e, F&& f) {
-    auto by_xbc = [&](auto lat, auto prec) -> hipError_t {
-        using L = decltype(lat);
-        using T = decltype(prec);
-        switch (e.xbc) {
-            case XBC_PRESSURE: return f(L{}, T{}, std::integral_constant<int, XBC_PRESSURE>{});
-            case XBC_OUTFLOW: return f(L{}, T{}, std::integral_constant<int, XBC_OUTFLOW>{});
-            default: return f(L{}, T{}, std::integral_constant<int, XBC_PERIODIC>{});
-        }
-    };
-    if (e.lattice == 0)
-        return e.precision == 0 ? by_xbc(D2Q9{}, double{}) : by_xbc(D2Q9{}, float{});
-    if (e.lattice == 2)
-        return e.precision == 0 ? by_xbc(D3Q15{}, double{}) : by_xbc(D3Q15{}, float{});
-    return e.precision == 0 ? by_xbc(D3Q19{}, double{}) : by_xbc(D3Q19{}, float{});
-}
 
 hipError_t launch_step(Engine& e, const Snapshot& in, const Snapshot& out,
                        const StepObjective& obj, void* rec) {
@@ -624,6 +577,13 @@ hipError_t launch_force_objective(Engine& e, const Snapshot& post, double* acc,
                            make_params<L, T>(e), tag, weight, acc);
         return hipGetLastError();
     });
+}
+
+hipError_t launch_sum_links(Engine& e, const double* v, double* partials, double* out) {
+    const unsigned nb = (unsigned)link_blocks(e);
+    hipLaunchKernelGGL(k_partial_sums, dim3(nb), dim3(BX), 0, e.stream, v, (uint32_t)e.n_links,
+                       partials);
+    return launch_sum_blocks(e, partials, nb, 1, out);
 }
 
 hipError_t launch_fill_nan(Engine& e, void* p, size_t n) {

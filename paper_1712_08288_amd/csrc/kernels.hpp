@@ -116,27 +116,45 @@ __device__ __forceinline__ void macc(T& acc, T v) {
     else if constexpr (C != 0) acc = fma(T(C), v, acc);
 }
 
-// Forcing term F_i = 3 w_i rho0 e_i.g of population I, and the seam term
-// w_i drho: from the tables (FTAB) or from the few runtime scalars they depend
-// on.  A kernel loads only the arguments it uses into scalar registers; the
-// scalars keep the adjoint and the FP64 step free of scalar-register spills,
-// the tables keep the FP32 step's arithmetic lowest (both measured).
+// A sum of such terms that starts with its first one: `0 + x` is an
+// instruction of its own, because x = -0 keeps the compiler from dropping it.
+template <class T>
+struct Sum {
+    T v = T(0);
+    bool any = false;   // known at compile time once the loops are unrolled
+    template <int C>
+    __device__ __forceinline__ void add(T x) {
+        if constexpr (C == 0) return;
+        if (any) macc<C>(v, x);
+        else if constexpr (C == 1) v = x;
+        else v = T(C) * x;
+        any = true;
+    }
+};
+
+// Forcing term F_i = 3 w_i rho0 e_i.g of population I subtracted from v, and
+// the seam term w_i drho times SIGN added to v: from the tables (FTAB) or from
+// the few runtime scalars they depend on.  A kernel loads only the arguments it
+// uses into scalar registers; the scalars keep the adjoint and the FP64 step
+// free of scalar-register spills, the tables keep the FP32 step's arithmetic
+// lowest (both measured).  The products are fused explicitly, so that every
+// kernel that takes a step rounds them alike, whatever it keeps in registers.
 template <class L, int I, bool FTAB, class T>
-__device__ __forceinline__ T force_of(const Params<L, T>& p) {
+__device__ __forceinline__ T minus_force(const Params<L, T>& p, T v) {
     if constexpr (FTAB) {
-        return p.force[I];
+        return v - p.force[I];
     } else {
         T eg = T(0);
         macc<L::E[I][0]>(eg, p.G[0]);
         macc<L::E[I][1]>(eg, p.G[1]);
         macc<L::E[I][2]>(eg, p.G[2]);
-        return T(L::W[I]) * eg;
+        return fma(-T(L::W[I]), eg, v);
     }
 }
-template <class L, int I, bool FTAB, class T>
-__device__ __forceinline__ T seam_of(const Params<L, T>& p) {
-    if constexpr (FTAB) return p.seam[I];
-    else return T(L::W[I]) * p.drho;
+template <class L, int I, bool FTAB, int SIGN, class T>
+__device__ __forceinline__ T plus_seam(const Params<L, T>& p, T v) {
+    if constexpr (FTAB) return SIGN > 0 ? v + p.seam[I] : v - p.seam[I];
+    else return fma(T(SIGN) * T(L::W[I]), p.drho, v);
 }
 
 // the step kernel's choice of the two forms above
@@ -202,22 +220,22 @@ __device__ __forceinline__ void moments_of(T x0, const T (&sp)[NPAIR<L>],
                                            const T (&dp)[NPAIR<L>], T (&m)[L::Q]) {
     unroll<L::Q>([&](auto K) {
         constexpr int k = decltype(K)::value;
-        T acc = 0;
+        Sum<T> acc;
         if constexpr (!L::conserved(k)) {
             if constexpr (DER<L>.even[k]) {
-                macc<TAB<L>.M[k][0]>(acc, x0);
+                acc.template add<TAB<L>.M[k][0]>(x0);
                 unroll<NPAIR<L>>([&](auto P) {
                     constexpr int pp = decltype(P)::value;
-                    macc<TAB<L>.M[k][DER<L>.pi[pp]]>(acc, sp[pp]);
+                    acc.template add<TAB<L>.M[k][DER<L>.pi[pp]]>(sp[pp]);
                 });
             } else {
                 unroll<NPAIR<L>>([&](auto P) {
                     constexpr int pp = decltype(P)::value;
-                    macc<TAB<L>.M[k][DER<L>.pi[pp]]>(acc, dp[pp]);
+                    acc.template add<TAB<L>.M[k][DER<L>.pi[pp]]>(dp[pp]);
                 });
             }
         }
-        m[k] = acc;
+        m[k] = acc.v;
     });
 }
 
@@ -226,15 +244,18 @@ template <class L, class T>
 __device__ __forceinline__ void conserved_of(T x0, const T (&sp)[NPAIR<L>],
                                              const T (&dp)[NPAIR<L>], T& rho, T (&j)[3]) {
     rho = x0;
-    j[0] = j[1] = j[2] = 0;
+    Sum<T> s[3];
     unroll<NPAIR<L>>([&](auto P) {
         constexpr int pp = decltype(P)::value;
         constexpr int i = DER<L>.pi[pp];
         rho += sp[pp];
-        macc<L::E[i][0]>(j[0], dp[pp]);
-        macc<L::E[i][1]>(j[1], dp[pp]);
-        macc<L::E[i][2]>(j[2], dp[pp]);
+        s[0].template add<L::E[i][0]>(dp[pp]);
+        s[1].template add<L::E[i][1]>(dp[pp]);
+        s[2].template add<L::E[i][2]>(dp[pp]);
     });
+    j[0] = s[0].v;
+    j[1] = s[1].v;
+    j[2] = s[2].v;
 }
 
 // m_k -= m^eq_k(drho, j) for the non-conserved rows (projection of Eq. (42))
@@ -265,24 +286,25 @@ __device__ __forceinline__ void subtract_equilibrium(T (&m)[L::Q], T rho, const 
 template <class L, class T>
 __device__ __forceinline__ void back_transform(const T (&r)[L::Q], T& e0,
                                                T (&ev)[NPAIR<L>], T (&od)[NPAIR<L>]) {
-    e0 = 0;
+    Sum<T> z;
     unroll<L::Q>([&](auto K) {
         constexpr int k = decltype(K)::value;
-        if constexpr (!L::conserved(k) && DER<L>.even[k]) macc<TAB<L>.M[k][0]>(e0, r[k]);
+        if constexpr (!L::conserved(k) && DER<L>.even[k]) z.template add<TAB<L>.M[k][0]>(r[k]);
     });
+    e0 = z.v;
     unroll<NPAIR<L>>([&](auto P) {
         constexpr int pp = decltype(P)::value;
         constexpr int i = DER<L>.pi[pp];
-        T a = 0, b = 0;
+        Sum<T> a, b;
         unroll<L::Q>([&](auto K) {
             constexpr int k = decltype(K)::value;
             if constexpr (!L::conserved(k)) {
-                if constexpr (DER<L>.even[k]) macc<TAB<L>.M[k][i]>(a, r[k]);
-                else macc<TAB<L>.M[k][i]>(b, r[k]);
+                if constexpr (DER<L>.even[k]) a.template add<TAB<L>.M[k][i]>(r[k]);
+                else b.template add<TAB<L>.M[k][i]>(r[k]);
             }
         });
-        ev[pp] = a;
-        od[pp] = b;
+        ev[pp] = a.v;
+        od[pp] = b.v;
     });
 }
 
@@ -318,7 +340,7 @@ __device__ __forceinline__ void collide(T (&f)[L::Q], const Params<L, T>& p,
         constexpr int pp = decltype(P)::value;
         constexpr int i = DER<L>.pi[pp];
         constexpr int ib = TAB<L>.opp[i];
-        const T o = od[pp] - force_of<L, i, FTAB>(p);    // F_ibar = -F_i
+        const T o = minus_force<L, i, FTAB>(p, od[pp]);    // F_ibar = -F_i
         f[i] = f[i] - ev[pp] - o;
         f[ib] = f[ib] - ev[pp] + o;
     });
@@ -438,8 +460,8 @@ __device__ __forceinline__ void pull_planes(const T* __restrict__ A, const Grid&
         f[i] = ldp<L::Q>(A, i, pl.template src<L, i>());
         if constexpr (XB == XBC_PRESSURE && L::E[i][0] != 0) {
             const int sg = seam_sign<L, i>(pos.ix, g.nx);
-            if (sg > 0) f[i] += seam_of<L, i, FTAB>(p);
-            else if (sg < 0) f[i] -= seam_of<L, i, FTAB>(p);
+            if (sg > 0) f[i] = plus_seam<L, i, FTAB, 1>(p, f[i]);
+            else if (sg < 0) f[i] = plus_seam<L, i, FTAB, -1>(p, f[i]);
         }
     });
 }
@@ -587,8 +609,8 @@ __device__ __forceinline__ T pull_one(const T* __restrict__ A, const Grid& g,
             const uint32_t src = (uint32_t)sx + g.nx * ((uint32_t)sy + g.ny * (uint32_t)sz);
             out = ldp<L::Q>(A, ii, src);
             if (XB == XBC_PRESSURE) {
-                if (sg > 0) out += seam_of<L, ii, false>(p);
-                else if (sg < 0) out -= seam_of<L, ii, false>(p);
+                if (sg > 0) out = plus_seam<L, ii, false, 1>(p, out);
+                else if (sg < 0) out = plus_seam<L, ii, false, -1>(p, out);
             }
         }
     });
