@@ -148,7 +148,9 @@ int lbm_set_geometry(lbm_t *h, const uint8_t *solid, int64_t n_links,
 
 /* Replace the per-link gamma and wall velocity of the current geometry (same
  * links, same order as given to lbm_set_geometry); recomputes coefficients.
- * Either pointer may be NULL to keep the current values. */
+ * Either pointer may be NULL to keep the current values, and either may be
+ * host or device memory (whose values must be there when the call is made).
+ * When a value is refused all stay as they were.  Synchronises. */
 int lbm_update_links(lbm_t *h, const double *q, const double *wall_u);
 
 /* Collision operators of Remark (1) (the boundary scheme does not depend on

@@ -3,8 +3,9 @@ hand-written adjoint.
 
     J = LBMObjective.apply(q, wall_u, g, s, problem)
 
-q (L,), wall_u (L, D), g (D,) and s (Q,) are float64 tensors (any device;
-they are copied to the host for the ABI, which is argument marshalling).
+q (L,), wall_u (L, D), g (D,) and s (Q,) are float tensors on any device (q
+and wall_u are handed to the library where they are, g and s through the
+host).
 `problem` is a Problem holding the solver, how to initialise it, the number
 of steps, the checkpoint interval and the objective.  forward() runs the
 steps with a snapshot every `every` steps (sqrt(n) checkpointing when
@@ -40,11 +41,20 @@ def _np(t):
     return t.detach().to("cpu", torch.float64).numpy()
 
 
+def _links(t):
+    """A per-link tensor as Solver.update_links takes it."""
+    if not t.is_cuda:
+        return _np(t)
+    t = t.detach().to(torch.float64).contiguous()
+    torch.cuda.current_stream(t.device).synchronize()   # the library has a stream of its own
+    return t
+
+
 class LBMObjective(torch.autograd.Function):
     @staticmethod
     def forward(ctx, q, wall_u, g, s, problem):
         sv = problem.solver
-        sv.update_links(_np(q), _np(wall_u))
+        sv.update_links(_links(q), _links(wall_u))
         sv.set_parameters(_np(s), _np(g))
         if problem.init is None:
             sv.init()

@@ -336,9 +336,21 @@ class Solver:
                   "set_geometry")
 
     def update_links(self, q=None, wall_u=None):
-        q = _f64(q)
-        wall_u = _f64(wall_u)
-        self._chk(_update_links(self._h, _ptr(q), _ptr(wall_u)), "update_links")
+        """q (L,), wall_u (L, D): arrays, or contiguous float64 device tensors
+        whose values are there when the call is made."""
+        nf, nl = self.counts()
+        ptr = []
+        for v, n in ((q, nl), (wall_u, nl * self.D)):
+            if hasattr(v, "is_cuda") and v.is_cuda:
+                if v.numel() != n or not v.is_contiguous() or str(v.dtype) != "torch.float64":
+                    raise ValueError("update_links: expected a contiguous float64 device tensor "
+                                     "of %d values" % n)
+                ptr.append(_p(v.data_ptr()))
+            else:
+                v = _f64(v)
+                ptr.append(v)
+        self._chk(_update_links(self._h, *(_ptr(v) if isinstance(v, np.ndarray) else v for v in ptr)),
+                  "update_links")
 
     def set_parameters(self, s=None, g=None):
         s = _f64(s, self.Q) if s is not None else None

@@ -65,30 +65,6 @@ bool lat_conserved(int lattice, int k) {
     return with_lattice(lattice, [&](auto l) { return decltype(l)::conserved(k); });
 }
 
-// ---- the free parameter l(gamma) (paper, Section 3 and Eq. (212)) ------------
-double l_of(int rule, double g) {
-    switch (rule) {
-        case LBM_L_GAMMA: return g;
-        case LBM_L_1P5GAMMA: return 1.5 * g;
-        case LBM_L_2GAMMA: return 2.0 * g;
-        case LBM_L_GAMMA2: return g * g;
-        case LBM_L_GAMMA2_PLUS_GAMMA: return g * g + g;
-        case LBM_L_ZERO: return 0.0;
-        default: return 2.0 * g - 1.0 > 0.0 ? 2.0 * g - 1.0 : 0.0;
-    }
-}
-double dl_of(int rule, double g) {
-    switch (rule) {
-        case LBM_L_GAMMA: return 1.0;
-        case LBM_L_1P5GAMMA: return 1.5;
-        case LBM_L_2GAMMA: return 2.0;
-        case LBM_L_GAMMA2: return 2.0 * g;
-        case LBM_L_GAMMA2_PLUS_GAMMA: return 2.0 * g + 1.0;
-        case LBM_L_ZERO: return 0.0;
-        default: return 2.0 * g - 1.0 > 0.0 ? 2.0 : 0.0;
-    }
-}
-
 template <class T>
 void free_dev(T*& p) {
     if (p) (void)hipFree((void*)p);
@@ -192,77 +168,77 @@ int sync(lbm_t* h) {
     return LBM_OK;
 }
 
-// Coefficients of Eq. (213) for every (sorted) link, and their gamma
-// derivatives along l = l(gamma).
-int compute_coefficients(lbm_t* h, std::vector<lbe::LinkCoef>& coef,
-                         std::vector<lbe::LinkDeriv>& der, std::vector<double>& c4v,
-                         std::vector<double>& c1d, std::vector<double>& d1d) {
-    Engine& e = h->e;
-    const int64_t L = e.n_links;
-    coef.resize(L);
-    der.resize(L);
-    c4v.resize(L);
-    c1d.resize(L);
-    d1d.resize(L);
-    const double b = e.b;
-    for (int64_t k = 0; k < L; ++k) {
-        const double g = e.q_h[k];
-        const int i = e.lk_dir_h[k];
-        const double l = l_of(e.l_rule, g);
-        const double lp = dl_of(e.l_rule, g);
-        const double lo = std::max(0.0, 2.0 * g - 1.0);
-        if (!(l >= lo - 1e-12 && l <= 2.0 * g + 1e-12))
-            return fail(h, LBM_EINVAL,
-                        "l(gamma) outside the convex band max(0,2g-1) <= l <= 2g at link " +
-                            std::to_string(e.perm[k]) + " (gamma = " + std::to_string(g) + ")");
-        const double den = 1.0 + l;
-        const double c1 = b * (1.0 + l - 2.0 * g) / den;
-        const double c2 = b * l / den;
-        const double c3 = b * (2.0 * g - l) / den;
-        const double c4 = b * 2.0 / den;
-        double ephi = 0.0;
-        for (int a = 0; a < e.D; ++a) ephi += lat_e(e.lattice, i, a) * e.wall_u_h[k * e.D + a];
-        const double unit = 3.0 * lat_w(e.lattice, i) * e.rho0 * ephi;
-        const double den2 = den * den;
-        const double d1 = b * ((lp - 2.0) * den - (1.0 + l - 2.0 * g) * lp) / den2;
-        const double d2 = b * lp / den2;
-        const double d3 = b * ((2.0 - lp) * den - (2.0 * g - l) * lp) / den2;
-        const double d4 = -2.0 * b * lp / den2;
-        // Eq. (211): the c1 term multiplies f_ibar(x_f, t+1) = f'_ibar(x_f + e_i, t)
-        // and is added at the next pull, unless x_f + e_i is solid
-        const bool defer = e.two_node && !e.ibar_is_link[k];
-        coef[k] = {defer ? 0.0 : c1, c2, c3, c4 * unit};
-        der[k] = {defer ? 0.0 : d1, d2, d3, d4 * unit};
-        c1d[k] = defer ? c1 : 0.0;
-        d1d[k] = defer ? d1 : 0.0;
-        c4v[k] = c4;
+template <class T>
+int alloc_dev(lbm_t* h, T*& p, size_t n) {
+    free_dev(p);
+    if (hipMalloc((void**)&p, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) {
+        p = nullptr;
+        return fail(h, LBM_ENOMEM, "device allocation failed");
     }
     return LBM_OK;
 }
 
-int upload_coefficients(lbm_t* h) {
+// The per-link tables of a geometry, one allocation for all of them.
+int alloc_links(lbm_t* h) {
     Engine& e = h->e;
-    std::vector<lbe::LinkCoef> coef;
-    std::vector<lbe::LinkDeriv> der;
-    std::vector<double> c4v, c1d, d1d;
-    int rc = compute_coefficients(h, coef, der, c4v, c1d, d1d);
+    const size_t L = (size_t)std::max<int64_t>(e.n_links, 1), LD = L * (size_t)e.D;
+    const int rc = alloc_dev(h, e.d_lktables, 2 * L + 2 * LD + 11 * L);
     if (rc) return rc;
-    if (e.precision == LBM_FP32) {
-        std::vector<lbe::LinkCoefT<float>> cf(coef.size());
-        for (size_t k = 0; k < coef.size(); ++k)
-            cf[k] = {(float)coef[k].c1, (float)coef[k].c2, (float)coef[k].c3,
-                     (float)coef[k].wall};
-        // the upload is asynchronous: keep the host copy alive until the sync
-        if ((rc = upload(h, e.d_lkcoef_f, cf.data(), cf.size()))) return rc;
+    double* p = e.d_lktables;
+    auto take = [&](size_t n) {
+        double* at = p;
+        p += n;
+        return at;
+    };
+    // the 16- and 32-byte records first
+    e.d_lkderiv = reinterpret_cast<lbe::LinkDeriv*>(take(4 * L));
+    double* coef = take(4 * L);
+    e.d_lkcoef = e.precision == LBM_FP64 ? reinterpret_cast<lbe::LinkCoefT<double>*>(coef) : nullptr;
+    e.d_lkcoef_f = e.precision == LBM_FP32 ? reinterpret_cast<lbe::LinkCoefT<float>*>(coef) : nullptr;
+    e.d_lkc4 = take(L);
+    e.d_lkc1d = take(L);
+    e.d_lkd1d = take(L);
+    e.d_q = take(L);
+    e.d_q_next = take(L);
+    e.d_wall_u = take(LD);
+    e.d_wall_u_next = take(LD);
+    return LBM_OK;
+}
+
+// Take gamma and phi (host or device; in the caller's order, or in link order
+// when `sorted`; null: unchanged), check them and make the link tables; the
+// old values stay when a value is refused.
+int take_links(lbm_t* h, const double* q, const double* wall_u, bool sorted) {
+    Engine& e = h->e;
+    const size_t L = (size_t)e.n_links;
+    if (L == 0) return LBM_OK;
+    int rc = ensure_scratch(h, (int64_t)(L * (1 + (size_t)e.D) + 1));
+    if (rc) return rc;
+    double* q_dev = e.d_scratch;
+    double* wall_dev = q_dev + L;
+    uint32_t* bad_dev = (uint32_t*)(wall_dev + L * (size_t)e.D);
+    HIPCHK(h, hipMemsetAsync(bad_dev, 0xFF, 8, e.stream));
+    if (q) HIPCHK(h, hipMemcpyAsync(q_dev, q, L * 8, hipMemcpyDefault, e.stream));
+    if (wall_u)
+        HIPCHK(h, hipMemcpyAsync(wall_dev, wall_u, L * (size_t)e.D * 8, hipMemcpyDefault, e.stream));
+    HIPCHK(h, lbe::launch_take_links(e, q ? q_dev : nullptr, wall_u ? wall_dev : nullptr,
+                                     sorted ? nullptr : e.d_perm, bad_dev));
+    uint32_t bad[2] = {0u, 0u};
+    HIPCHK(h, hipMemcpyAsync(bad, bad_dev, 8, hipMemcpyDeviceToHost, e.stream));
+    if ((rc = sync(h))) return rc;
+    if (bad[0] < L) return fail(h, LBM_EINVAL, "q must lie in (0, 1]");
+    if (bad[1] < L) {
+        double g = 0.0;
+        HIPCHK(h, hipMemcpyAsync(&g, e.d_q_next + bad[1], 8, hipMemcpyDeviceToHost, e.stream));
         if ((rc = sync(h))) return rc;
-    } else if ((rc = upload(h, e.d_lkcoef, coef.data(), coef.size()))) {
-        return rc;
+        return fail(h, LBM_EINVAL,
+                    "l(gamma) outside the convex band max(0,2g-1) <= l <= 2g at link " +
+                        std::to_string(e.perm[bad[1]]) + " (gamma = " + std::to_string(g) + ")");
     }
-    if ((rc = upload(h, e.d_lkderiv, der.data(), der.size()))) return rc;
-    if ((rc = upload(h, e.d_lkc4, c4v.data(), c4v.size()))) return rc;
-    if ((rc = upload(h, e.d_lkc1d, c1d.data(), c1d.size()))) return rc;
-    if ((rc = upload(h, e.d_lkd1d, d1d.data(), d1d.size()))) return rc;
-    return sync(h);
+    std::swap(e.d_q, e.d_q_next);
+    std::swap(e.d_wall_u, e.d_wall_u_next);
+    HIPCHK(h, lbe::launch_link_coefficients(e));
+    return LBM_OK;
 }
 
 // Captured step loops become invalid when kernel arguments change.
@@ -381,11 +357,15 @@ int set_tiles(lbm_t* h, const int (*vel)[3]) {
     static_assert(sizeof(lbe::TileLink) == sizeof(uint4), "device layout");
     int rc;
     HIPCHK(h, lbe::tile_setup(e));
-    if ((rc = upload(h, e.d_tile_first, links.first.data(), links.first.size()))) return rc;
+    // one table: the links, then the offsets in whole entries
+    const size_t nl = links.link.size();
+    links.link.resize(nl + (links.first.size() + 3) / 4);
+    std::memcpy(links.link.data() + nl, links.first.data(), links.first.size() * 4);
     if ((rc = upload(h, e.d_tile_link, reinterpret_cast<const uint4*>(links.link.data()),
                      links.link.size())))
         return rc;
-    return sync(h);   // the uploads read `links`
+    e.d_tile_first = reinterpret_cast<const uint32_t*>(e.d_tile_link + nl);
+    return sync(h);   // the upload reads `links`
 }
 
 // How many of the next `left` steps from time t one launch on tiles may take
@@ -817,8 +797,6 @@ int lbm_set_geometry(lbm_t* h, const uint8_t* solid, int64_t n_links,
     e.obj_kind = LBM_OBJ_NONE;   // an objective refers to the previous geometry
     e.lk_node_h = tab.node;
     e.lk_dir_h = tab.dir;
-    e.q_h = tab.q;
-    e.wall_u_h = tab.wall_u;
     e.tag_h = tab.tag;
     e.n_tags = tab.n_tags;
     e.ibar_is_link = tab.ibar_is_link;
@@ -847,7 +825,9 @@ int lbm_set_geometry(lbm_t* h, const uint8_t* solid, int64_t n_links,
         if ((rc = upload(h, e.d_perm, p32.data(), p32.size()))) return rc;
     }
     if ((rc = upload(h, e.d_lktag, e.tag_h.data(), e.tag_h.size()))) return rc;
-    if ((rc = upload_coefficients(h))) return rc;
+    if ((rc = upload(h, e.d_lkibar, e.ibar_is_link.data(), e.ibar_is_link.size()))) return rc;
+    if ((rc = alloc_links(h))) return rc;
+    if ((rc = take_links(h, tab.q.data(), tab.wall_u.data(), true))) return rc;
     for (auto& b : e.buf) {
         if (b.wa) (void)hipFree(b.wa);
         if (hipMalloc(&b.wa, wa_bytes(e)) != hipSuccess) {
@@ -868,27 +848,9 @@ int lbm_update_links(lbm_t* h, const double* q, const double* wall_u) {
     if (!h) return LBM_EINVAL;
     Engine& e = h->e;
     if (!e.has_geometry) return fail(h, LBM_ESTATE, "no geometry");
-    std::vector<double> q_old = e.q_h, u_old = e.wall_u_h;
-    for (int64_t k = 0; k < e.n_links; ++k) {
-        const int64_t p = e.perm[k];
-        if (q) {
-            if (!(q[p] > 0.0 && q[p] <= 1.0)) {
-                e.q_h = q_old;
-                return fail(h, LBM_EINVAL, "q must lie in (0, 1]");
-            }
-            e.q_h[k] = q[p];
-        }
-        if (wall_u)
-            for (int a = 0; a < e.D; ++a) e.wall_u_h[k * e.D + a] = wall_u[p * e.D + a];
-    }
     HIPCHK(h, hipStreamSynchronize(e.stream));
     drop_graphs(e);
-    const int rc = upload_coefficients(h);
-    if (rc) {
-        e.q_h = q_old;
-        e.wall_u_h = u_old;
-    }
-    return rc;
+    return take_links(h, q, wall_u, false);
 }
 
 int lbm_set_parameters(lbm_t* h, const double* s, const double* g) {
@@ -1195,10 +1157,11 @@ int lbm_set_objective(lbm_t* h, int kind, int32_t tag, int64_t t_begin, int64_t 
     e.obj_t0 = t_begin;
     e.obj_t1 = t_end;
     const int64_t len = kind == LBM_OBJ_FORCE_X ? e.n_links : lbe::step_blocks(e);
-    free_dev(e.d_obj_acc);
+    if (kind == LBM_OBJ_NONE || e.obj_acc_len != len) free_dev(e.d_obj_acc);
     e.obj_acc_len = 0;
     if (kind != LBM_OBJ_NONE) {
-        if (hipMalloc((void**)&e.d_obj_acc, (size_t)std::max<int64_t>(len, 1) * 8) != hipSuccess) {
+        if (!e.d_obj_acc &&
+            hipMalloc((void**)&e.d_obj_acc, (size_t)std::max<int64_t>(len, 1) * 8) != hipSuccess) {
             e.d_obj_acc = nullptr;
             return fail(h, LBM_ENOMEM, "objective accumulator allocation failed");
         }
@@ -1490,18 +1453,13 @@ int lbm_destroy(lbm_t* h) {
     free_dev(e.d_info);
     free_dev(e.d_wave);
     free_dev(e.d_wact);
+    free_dev(e.d_lktables);
     free_dev(e.d_lkdir);
-    free_dev(e.d_tile_first);
+    free_dev(e.d_lkibar);
     free_dev(e.d_tile_link);
     free_dev(e.d_lknode);
     free_dev(e.d_perm);
     free_dev(e.d_lktag);
-    free_dev(e.d_lkcoef);
-    free_dev(e.d_lkcoef_f);
-    free_dev(e.d_lkderiv);
-    free_dev(e.d_lkc4);
-    free_dev(e.d_lkc1d);
-    free_dev(e.d_lkd1d);
     free_dev(e.d_obj_acc);
     free_dev(e.d_gq);
     e.d_gs = nullptr;

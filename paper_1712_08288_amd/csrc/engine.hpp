@@ -78,7 +78,6 @@ struct Engine {
     std::vector<int64_t> perm;          // sorted link k -> caller index
     std::vector<int64_t> lk_node_h;     // sorted
     std::vector<int8_t> lk_dir_h;
-    std::vector<double> q_h, wall_u_h;  // sorted, wall_u (L, D)
     std::vector<int32_t> tag_h;
 
     uint32_t* d_info = nullptr;         // per node: bit 31 solid, bits 19..30 link offset
@@ -86,7 +85,13 @@ struct Engine {
     uint2* d_wave = nullptr;            // per 64-node wave of a node launch: kind, first link
     uint4* d_wact = nullptr;            // the adjoint's non-idle waves in memory order:
     int64_t n_wact = 0;                 // {id, kind | links << 2, first link, 0}
+    double* d_lktables = nullptr;       // holds the per-link tables that follow:
+    double* d_q = nullptr;              // gamma (L) and phi (L, D) in link order
+    double* d_wall_u = nullptr;
+    double* d_q_next = nullptr;         // the same being taken, until checked
+    double* d_wall_u_next = nullptr;
     uint8_t* d_lkdir = nullptr;
+    uint8_t* d_lkibar = nullptr;        // (x_f, ibar) is a link too
     int32_t* d_lknode = nullptr;
     int32_t* d_perm = nullptr;          // sorted link k -> caller index
     int32_t* d_lktag = nullptr;
@@ -102,8 +107,8 @@ struct Engine {
     double* d_lkd1d = nullptr;          // its gamma derivative
 
     TilePlan tiles;                     // several steps per launch (halo 0: one)
-    uint32_t* d_tile_first = nullptr;   // the links of its regions (TileLinks)
-    uint4* d_tile_link = nullptr;
+    uint4* d_tile_link = nullptr;       // the links of its regions (TileLinks)
+    const uint32_t* d_tile_first = nullptr;   // (behind them)
 
     // state: post-collision array A and link slots of the current time
     Snapshot buf[2];
@@ -255,6 +260,15 @@ hipError_t noalloc_scratch(int device, double** out);
 int64_t step_blocks(const Engine& e);       // logical blocks of a node launch
 int64_t adjoint_blocks(const Engine& e);    // blocks of the two adjoint launches together
 int64_t link_blocks(const Engine& e);       // blocks of a link launch
+
+// ---- launchers (links.hip) ----------------------------------------------------
+// gamma and phi (device, caller's order, or link order with perm null; null:
+// unchanged) into d_q_next and d_wall_u_next.  bad[0], bad[1] (set to all ones
+// before): the first link whose gamma, or whose l(gamma), is out of range.
+hipError_t launch_take_links(Engine& e, const double* q, const double* wall_u, const int32_t* perm,
+                             uint32_t* bad);
+// the link tables from d_q and d_wall_u
+hipError_t launch_link_coefficients(Engine& e);
 
 // ---- launchers (tiles.hip) ----------------------------------------------------
 // What a block of a launch on tiles can hold for this handle.

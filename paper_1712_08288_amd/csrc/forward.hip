@@ -449,9 +449,13 @@ __global__ void __launch_bounds__(BX)
 k_sum_blocks(const double* __restrict__ partials, uint32_t rows, uint32_t cols,
              double* __restrict__ out) {
     const uint32_t c = blockIdx.x;
-    double s = 0;
-    for (uint32_t r = threadIdx.x; r < rows; r += BX) s += partials[(size_t)r * cols + c];
-    s = block_sum(s);
+    // four sums, so that four loads are in flight
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (uint32_t r = threadIdx.x; r < rows; r += 4 * BX)
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+            if (r + j * BX < rows) v[j] += partials[(size_t)(r + j * BX) * cols + c];
+    const double s = block_sum((v[0] + v[1]) + (v[2] + v[3]));
     if (threadIdx.x == 0) out[c] = s;
 }
 
