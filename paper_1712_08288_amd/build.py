@@ -13,7 +13,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(OUT_DIR, "liblbm.so")
-SOURCES = ["api.cpp", "geometry.cpp", "tiling.cpp", "forward.hip", "tiles.hip", "links.hip", "adjoint.hip", "stream.hip"]
+SOURCES = ["api.cpp", "geometry.cpp", "tiling.cpp", "forward.hip", "tiles.hip", "links.hip", "adjoint.hip", "adjoint_d2q9.hip",
+           "adjoint_d3q15.hip", "adjoint_d3q19.hip", "stream.hip"]
 ARCH = os.environ.get("LBM_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [
