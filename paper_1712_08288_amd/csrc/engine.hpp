@@ -175,6 +175,7 @@ struct Engine {
     // scratch for reductions and host transfers
     double* d_scratch = nullptr;
     int64_t scratch_len = 0;
+    double* pinned = nullptr;           // host memory that small results are written to
 
     hipStream_t stream = nullptr;
     hipStream_t own_stream = nullptr;
