@@ -199,24 +199,6 @@ __device__ __forceinline__ int wave_sum_column(uint32_t lane) {
     return first && valid > 0 ? at : -1;
 }
 
-// dst[c] = before + scale(c) times the block's sum of v[c], before = dst[c] read
-// by thread c in advance
-template <int NC, class Scale>
-__device__ __forceinline__ void block_accumulate(double (&v)[NC], double before,
-                                                 double* __restrict__ dst, Scale&& scale) {
-    __shared__ double part[BX / 64][NC];
-    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
-    wave_sums<NC, 32>(v, lane);
-    const int column = wave_sum_column<NC>(lane);
-    if (column >= 0) part[wid][column] = v[0];
-    __syncthreads();
-    if (threadIdx.x < NC) {
-        double s = 0;
-        for (int w = 0; w < BX / 64; ++w) s += part[w][threadIdx.x];
-        dst[threadIdx.x] = before + s * scale((int)threadIdx.x);
-    }
-}
-
 // Links past the 64th of a mixed wave are handled by the lane of their node y
 // (the first 64 go through the wave's LDS slab).  The adjoint a_k of link
 // k = (y, i), drag term dfx included.
@@ -295,15 +277,19 @@ __device__ __forceinline__ NodePos node_of_wave(const Grid& g, const WaveList& w
 // planes of U) instead of pulling the Q populations of f(y, t), and the
 // link values of the gradients come from the same step record: A, wa and
 // nxt are not read.
-// FP64 on step records asks for 4 waves per SIMD: the kernel needs 130
-// VGPRs, and fitting 128 (two values spilled to scratch) made the reverse
-// step 3.5% faster at 256^3.  FP64 D3 reading states asks for 3 (180 to 168
-// VGPRs): 96x64x64 with the rate gradients 61.3 -> 54.4 us, the products
-// below included.  The other variants are left to the compiler (forcing more
-// waves on them spilled more and was slower).
+// Waves per SIMD asked of the compiler, where it stops just short of them:
+// FP64 on step records 4 (130 VGPRs fitted into 128 made the reverse step 3.5%
+// faster at 256^3); with the rate gradients FP64 D3 3, FP32 D3 4 and FP32 D2 6.
+// The others are left to the compiler (forcing more waves on them spilled more
+// and was slower).
+template <class L, class T>
+constexpr int adjoint_waves(bool want_ds, bool um) {
+    if (sizeof(T) == 8) return um ? 4 : L::D == 3 ? 3 : 1;
+    return want_ds ? (L::D == 3 ? 4 : 6) : 1;
+}
 template <class L, class T, int XB, bool WANT_DS, bool ROWS, bool UM>
 __global__ void __launch_bounds__(BX)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && UM ? 4 : sizeof(T) == 8 && L::D == 3 ? 3 : 1)))
+__attribute__((amdgpu_waves_per_eu(adjoint_waves<L, T>(WANT_DS, UM))))
 k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
           const T* __restrict__ nxt,
           const T* __restrict__ lam_in, T* __restrict__ lam_out,
@@ -314,7 +300,7 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
     constexpr int Q = L::Q, D = L::D, NP = NPAIR<L>;
     static_assert(!(UM && WANT_DS), "the rate gradients need the forward populations");
     constexpr int NC = D + Q;                 // layout of the per-block sums
-    constexpr int NR = WANT_DS ? NC : D;      // columns reduced here
+    constexpr int NK = Q - D - 1;             // rows with a rate
     __shared__ LinkStage<T> stage[BX / 64];
     // the link lanes' a_k, parked while the node's work runs (registers are
     // scarcest there), and the f_ibar(y, t) that the nodes' lanes hand them
@@ -331,9 +317,10 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
     const uint32_t wbase = __builtin_amdgcn_readfirstlane(wm.z);
     const NodePos pos = node_of_wave<ROWS>(g, wl, w, lane, active);
     LinkStage<T>& st = stage[wid];
-    double acc[NR];
+    double acc[D];
 #pragma unroll
-    for (int c = 0; c < NR; ++c) acc[c] = 0.0;
+    for (int c = 0; c < D; ++c) acc[c] = 0.0;
+    double ds_sum = 0.0;                      // of the rate row of wave_sum_column
     // What a read-modify-write at the kernel's end needs is read in advance
     // where that costs no occupancy (reverse step reading states, D2Q9 FP64
     // 512x256: 16.1 -> 15.3 us); on records it costs a wave per SIMD (66
@@ -341,8 +328,21 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
     constexpr bool EARLY = !UM && (sizeof(T) == 4 || D == 2);
     double* const sums = gglob + (size_t)blockIdx.x * NC;
     double before = 0.0;
-    if constexpr (EARLY)
-        if (threadIdx.x < NR) before = sums[threadIdx.x];
+    // (thread c adds gradient column c below D, then the rows with a rate)
+    int column = (int)threadIdx.x < D ? (int)threadIdx.x : -1;
+    double scale = 3.0 * p.rho0_d;
+    if constexpr (WANT_DS) {
+        int c = D;
+        unroll<Q>([&](auto K) {
+            constexpr int kk = decltype(K)::value;
+            if constexpr (!L::conserved(kk))
+                if ((int)threadIdx.x == c++) {
+                    column = D + kk;
+                    scale = -1.0 / (double)TAB<L>.norm[kk];
+                }
+        });
+    }
+    if (EARLY && column >= 0) before = sums[column];
 
     // One wave's work.  Plain and mixed waves take separate paths from the
     // start (their own loads included), so that each path's registers are
@@ -389,10 +389,13 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
             });
         }
 
-        // one fluid node; PLAIN: the whole wave is fluid without cut links.  In
+        // one node per lane; PLAIN: the whole wave is fluid without cut links.  In
         // a mixed wave nl.base is relative to the wave's first link and f already
-        // holds the link slots.
-        auto node = [&](auto plain_c, const NodeLinks& nl) {
+        // holds the link slots; its solid lanes go along (sol), so that the wave
+        // stays whole for the sums and writes whole lines of lam_out: they add
+        // nothing and store NaN (nothing reads lambda at solid nodes; partial
+        // lines cost HBM read-modify-write cycles).
+        auto node = [&](auto plain_c, const NodeLinks& nl, bool sol) {
             constexpr bool PLAIN = decltype(plain_c)::value;
             // forward state f(y, t) and its velocity (UM: the recorded one)
             T sp[NP], dp[NP];
@@ -454,7 +457,7 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
                     if constexpr (XB == XBC_OUTFLOW && L::E[i][0] == 1) lost = lost || ps.x_out;
                     mu[i] = lost ? T(0) : lg[i];
                     if constexpr (XB == XBC_OUTFLOW && L::E[i][0] == -1) {
-                        if (ps.x_out) {
+                        if (ps.x_out && !sol) {
                             const uint32_t n2 = ps.template dst_clamped<L, i>(pos.ix);
                             if (!is_solid(nm.info[n2])) mu[i] += ldp<Q>(lam_in, i, n2);
                         }
@@ -497,11 +500,17 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
             moments_of<L, T>(mu[0], smu, dmu, qm);
             if constexpr (WANT_DS) {
                 // dJ/ds_k -= (M mu)_k (M (f - f^eq))_k / |M_k|^2 (the factor
-                // on the sums: a division here would cost more than the rest)
+                // on the sums: a division here would cost more than the rest),
+                // summed over the wave at once, so that one value is held
+                double prod[NK];
+                int c = 0;
                 unroll<Q>([&](auto K) {
                     constexpr int kk = decltype(K)::value;
-                    if constexpr (!L::conserved(kk)) acc[D + kk] = (double)qm[kk] * (double)neq[kk];
+                    if constexpr (!L::conserved(kk))
+                        prod[c++] = !PLAIN && sol ? 0.0 : (double)qm[kk] * (double)neq[kk];
                 });
+                wave_sums<NK, 32>(prod, lane);
+                ds_sum = prod[0];
             }
 
             // dJ/dg += 3 rho0 sum_i w_i e_i mu_i (pair form: w_i e_i (mu_i - mu_ibar)),
@@ -519,7 +528,8 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
                     macc<L::E[i][2]>(sg3[2], t);
                 });
 #pragma unroll
-                for (int al = 0; al < D; ++al) acc[al] += (double)sg3[al];
+                for (int al = 0; al < D; ++al)
+                    acc[al] += !PLAIN && sol ? 0.0 : (double)sg3[al];
             };
             if constexpr (!PLAIN) add_dg();
 
@@ -548,29 +558,36 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
                 constexpr int kk = decltype(K)::value;
                 r[kk] = L::conserved(kk) ? T(0) : qm[kk] * p.rate[kk];
             });
+            // J^T v = (d m^eq / df)^T r = as + b.e_j: with m^eq_k = A_k drho + B_k.j
+            // + C_k (jj) / rho0 (Derived), as = sum_k A_k r_k and
+            // b = sum_k r_k (B_k + d (C_k (jj) / rho0) / dj), taken from the
+            // moments instead of the populations of v (a third of the operations)
+            T as, b[3];
+            {
+                Sum<T> sa, sb[3], sc[6];
+                unroll<Q>([&](auto K) {
+                    constexpr int kk = decltype(K)::value;
+                    if constexpr (!L::conserved(kk)) {
+                        if constexpr (DER<L>.A[kk] != 0.0) sa.term(T(DER<L>.A[kk]), r[kk]);
+                        unroll<3>([&](auto X) {
+                            constexpr int x = decltype(X)::value;
+                            if constexpr (DER<L>.B[kk][x] != 0.0)
+                                sb[x].term(T(DER<L>.B[kk][x]), r[kk]);
+                        });
+                        unroll<6>([&](auto C) {
+                            constexpr int c = decltype(C)::value;
+                            if constexpr (DER<L>.C[kk][c] != 0.0)
+                                sc[c].term(T(DER<L>.C[kk][c]), r[kk]);
+                        });
+                    }
+                });
+                as = sa.v;
+                b[0] = sb[0].v + (T(2) * sc[0].v * u[0] + sc[3].v * u[1] + sc[5].v * u[2]);
+                b[1] = sb[1].v + (sc[3].v * u[0] + T(2) * sc[1].v * u[1] + sc[4].v * u[2]);
+                b[2] = sb[2].v + (sc[5].v * u[0] + sc[4].v * u[1] + T(2) * sc[2].v * u[2]);
+            }
             T e0, ev[NP], od[NP];
             back_transform<L, T>(r, e0, ev, od);
-            // J^T v = as + b.e_j with as = sum w_i v_i and
-            // b = sum_i w_i v_i (3 e_i + 9 (e_i.u) e_i) - 3 u as
-            T as = T(L::W[0]) * e0;
-            T b[3] = {0, 0, 0};
-            unroll<NP>([&](auto P) {
-                constexpr int pp = decltype(P)::value;
-                constexpr int i = DER<L>.pi[pp];
-                const T w2 = T(2.0 * L::W[i]);
-                as += w2 * ev[pp];
-                T eu = 0;
-                macc<L::E[i][0]>(eu, u[0]);
-                macc<L::E[i][1]>(eu, u[1]);
-                macc<L::E[i][2]>(eu, u[2]);
-                const T t = w2 * (T(3) * od[pp] + T(9) * eu * ev[pp]);
-                macc<L::E[i][0]>(b[0], t);
-                macc<L::E[i][1]>(b[1], t);
-                macc<L::E[i][2]>(b[2], t);
-            });
-            b[0] -= T(3) * u[0] * as;
-            b[1] -= T(3) * u[1] * as;
-            b[2] -= T(3) * u[2] * as;
             const T wux = (T)a.w_ux;
             // pressure drop: the same term for every population of the node
             if (a.obj_kind == 3)
@@ -582,7 +599,9 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
                 macc<L::E[jd][1]>(out, b[1]);
                 macc<L::E[jd][2]>(out, b[2]);
                 if (a.obj_kind == 2) macc<L::E[jd][0]>(out, wux);
-                stp_nt<Q>(lam_out, jd, pos.n, out);
+                if constexpr (!PLAIN)
+                    if (sol) out = (T)__builtin_nan("");
+                if (PLAIN || live) stp_nt<Q>(lam_out, jd, pos.n, out);
             };
             finish(std::integral_constant<int, 0>{}, e0);
             unroll<NP>([&](auto P) {
@@ -596,7 +615,7 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
         };
 
         if constexpr (!MX) {
-            node(std::true_type{}, NodeLinks{0u, 0u});
+            node(std::true_type{}, NodeLinks{0u, 0u}, false);
         } else {
             // link lanes: the link's adjoint a_k = lambda_i(y, t+1) and (reading
             // states) the forward step's stored f'_i(y, t), f'_ibar(y, t)
@@ -654,7 +673,7 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
                     ak_park[wid][lane] = ak;
             }
             wave_lds_sync();
-            if (!sol) node(std::false_type{}, nl);
+            node(std::false_type{}, nl, sol);
             wave_lds_sync();
             if constexpr (!UM)
                 if (link_lane) {
@@ -664,15 +683,6 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
                                              d3 * (double)fpib);
                     lgr.g[lgr.L1 + kl] = gs + ak_l * p.wall_scale;
                 }
-            // the solid lanes store NaN (nothing reads lambda at solid nodes) so
-            // that the wave writes whole lines of lam_out: partial lines cost
-            // HBM read-modify-write cycles
-            if (live && sol) {
-                unroll<Q>([&](auto I) {
-                    constexpr int i = decltype(I)::value;
-                    stp_nt<Q>(lam_out, i, pos.n, (T)__builtin_nan(""));
-                });
-            }
         }
     };
     if (active) {
@@ -682,18 +692,20 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
             run(std::true_type{});
     }
 
-    // every wave of the block reaches the barrier inside
-    if constexpr (!EARLY)
-        if (threadIdx.x < NR) before = sums[threadIdx.x];
-    block_accumulate<NR>(acc, before, sums, [&](int c) {
-        double f = 3.0 * p.rho0_d;                // dJ/dg
-        if constexpr (WANT_DS)
-            unroll<Q>([&](auto K) {
-                constexpr int kk = decltype(K)::value;
-                if (c == D + kk) f = -1.0 / (double)TAB<L>.norm[kk];
-            });
-        return f;
-    });
+    // the waves' sums, then the block's
+    __shared__ double part[BX / 64][D + NK];
+    wave_sums<D, 32>(acc, lane);
+    const int col = wave_sum_column<D>(lane), row = wave_sum_column<NK>(lane);
+    if (col >= 0) part[wid][col] = acc[0];
+    if constexpr (WANT_DS)
+        if (row >= 0) part[wid][D + row] = ds_sum;
+    __syncthreads();
+    if (column >= 0) {
+        double s = 0.0;
+        for (int w = 0; w < BX / 64; ++w) s += part[w][threadIdx.x];
+        if (!EARLY) before = sums[column];
+        sums[column] = before + s * scale;
+    }
 }
 
 // The node kernel of one reverse step for the handle's precision, x boundary

@@ -130,6 +130,11 @@ struct Sum {
         else v = T(C) * x;
         any = true;
     }
+    // a term with a real coefficient
+    __device__ __forceinline__ void term(T c, T x) {
+        v = any ? fma(c, x, v) : c * x;
+        any = true;
+    }
 };
 
 // Forcing term F_i = 3 w_i rho0 e_i.g of population I subtracted from v, and
@@ -214,48 +219,53 @@ __device__ __forceinline__ void pair_split(const T (&x)[L::Q], T (&sp)[NPAIR<L>]
     });
 }
 
-// (M x)_k for the non-conserved rows from the pair form of x
+// the sum over one class of pairs of a group's pattern times x (sp for an even
+// group, dp for an odd one)
+template <class L, int G, int C, class T>
+__device__ __forceinline__ T class_sum(const T (&x)[NPAIR<L>]) {
+    Sum<T> acc;
+    unroll<NPAIR<L>>([&](auto P) {
+        constexpr int pp = decltype(P)::value;
+        if constexpr (FAC<L>.cls[pp] == C) acc.template add<FAC<L>.v[G][pp]>(x[pp]);
+    });
+    return acc.v;
+}
+
+// (M x)_k from the pair form of x
+template <class L, int K, class T>
+__device__ __forceinline__ T moment_of(T x0, const T (&sp)[NPAIR<L>], const T (&dp)[NPAIR<L>]) {
+    Sum<T> acc;
+    unroll<FAC<L>.nclass>([&](auto C) {
+        constexpr int c = decltype(C)::value;
+        if constexpr (FAC<L>.c[K][c] != 0)
+            acc.template add<FAC<L>.c[K][c]>(
+                class_sum<L, FAC<L>.group[K], c, T>(DER<L>.even[K] ? sp : dp));
+    });
+    acc.template add<TAB<L>.M[K][0]>(x0);
+    return acc.v;
+}
+
+// the non-conserved rows
 template <class L, class T>
 __device__ __forceinline__ void moments_of(T x0, const T (&sp)[NPAIR<L>],
                                            const T (&dp)[NPAIR<L>], T (&m)[L::Q]) {
     unroll<L::Q>([&](auto K) {
         constexpr int k = decltype(K)::value;
-        Sum<T> acc;
-        if constexpr (!L::conserved(k)) {
-            if constexpr (DER<L>.even[k]) {
-                acc.template add<TAB<L>.M[k][0]>(x0);
-                unroll<NPAIR<L>>([&](auto P) {
-                    constexpr int pp = decltype(P)::value;
-                    acc.template add<TAB<L>.M[k][DER<L>.pi[pp]]>(sp[pp]);
-                });
-            } else {
-                unroll<NPAIR<L>>([&](auto P) {
-                    constexpr int pp = decltype(P)::value;
-                    acc.template add<TAB<L>.M[k][DER<L>.pi[pp]]>(dp[pp]);
-                });
-            }
-        }
-        m[k] = acc.v;
+        if constexpr (L::conserved(k)) m[k] = T(0);
+        else m[k] = moment_of<L, k, T>(x0, sp, dp);
     });
 }
 
-// density deviation and momentum sum_i e_i x_i from the pair form
+// density deviation and momentum sum_i e_i x_i from the pair form (rows 0, 3,
+// 5 and, in three dimensions, 7)
 template <class L, class T>
 __device__ __forceinline__ void conserved_of(T x0, const T (&sp)[NPAIR<L>],
                                              const T (&dp)[NPAIR<L>], T& rho, T (&j)[3]) {
-    rho = x0;
-    Sum<T> s[3];
-    unroll<NPAIR<L>>([&](auto P) {
-        constexpr int pp = decltype(P)::value;
-        constexpr int i = DER<L>.pi[pp];
-        rho += sp[pp];
-        s[0].template add<L::E[i][0]>(dp[pp]);
-        s[1].template add<L::E[i][1]>(dp[pp]);
-        s[2].template add<L::E[i][2]>(dp[pp]);
-    });
-    j[0] = s[0].v;
-    j[1] = s[1].v;
-    j[2] = s[2].v;
+    rho = moment_of<L, 0, T>(x0, sp, dp);
+    j[0] = moment_of<L, 3, T>(x0, sp, dp);
+    j[1] = moment_of<L, 5, T>(x0, sp, dp);
+    if constexpr (L::D == 3) j[2] = moment_of<L, 7, T>(x0, sp, dp);
+    else j[2] = T(0);
 }
 
 // m_k -= m^eq_k(drho, j) for the non-conserved rows (projection of Eq. (42))
@@ -292,16 +302,34 @@ __device__ __forceinline__ void back_transform(const T (&r)[L::Q], T& e0,
         if constexpr (!L::conserved(k) && DER<L>.even[k]) z.template add<TAB<L>.M[k][0]>(r[k]);
     });
     e0 = z.v;
+    // per group and class, what its rows add to the pattern
+    T rc[FAC<L>.ngroup][FAC<L>.nclass];
+    bool any[FAC<L>.ngroup][FAC<L>.nclass];   // known at compile time
+    unroll<FAC<L>.ngroup>([&](auto G) {
+        constexpr int g = decltype(G)::value;
+        unroll<FAC<L>.nclass>([&](auto C) {
+            constexpr int c = decltype(C)::value;
+            Sum<T> acc;
+            unroll<L::Q>([&](auto K) {
+                constexpr int k = decltype(K)::value;
+                if constexpr (!L::conserved(k) && FAC<L>.group[k] == g)
+                    acc.template add<FAC<L>.c[k][c]>(r[k]);
+            });
+            rc[g][c] = acc.v;
+            any[g][c] = acc.any;
+        });
+    });
     unroll<NPAIR<L>>([&](auto P) {
         constexpr int pp = decltype(P)::value;
-        constexpr int i = DER<L>.pi[pp];
+        constexpr int c = FAC<L>.cls[pp];
         Sum<T> a, b;
-        unroll<L::Q>([&](auto K) {
-            constexpr int k = decltype(K)::value;
-            if constexpr (!L::conserved(k)) {
-                if constexpr (DER<L>.even[k]) a.template add<TAB<L>.M[k][i]>(r[k]);
-                else b.template add<TAB<L>.M[k][i]>(r[k]);
-            }
+        unroll<FAC<L>.ngroup>([&](auto G) {
+            constexpr int g = decltype(G)::value;
+            if constexpr (FAC<L>.v[g][pp] != 0)
+                if (any[g][c]) {
+                    if constexpr (FAC<L>.even[g]) a.template add<FAC<L>.v[g][pp]>(rc[g][c]);
+                    else b.template add<FAC<L>.v[g][pp]>(rc[g][c]);
+                }
         });
         ev[pp] = a.v;
         od[pp] = b.v;

@@ -297,7 +297,9 @@ k_tile_steps(const T* __restrict__ A, const T* __restrict__ waA, TileOut<T> out,
                 if (store)
                     unroll<Q>([&](auto I) {
                         constexpr int i = decltype(I)::value;
-                        stp_nt<Q>(B, i, nn, sol ? nan : f[m][i]);
+                        // (a pointer read from LDS: say that it is global)
+                        typedef __attribute__((address_space(1))) T G;
+                        __builtin_nontemporal_store(sol ? nan : f[m][i], (G*)B + pop_at<Q>(i, nn));
                     });
             }
         }
@@ -306,6 +308,9 @@ k_tile_steps(const T* __restrict__ A, const T* __restrict__ waA, TileOut<T> out,
             __syncthreads();
             const double ws = wall_scale[s];
             T* __restrict__ waB = out_wa[s];
+            // keeps the conversions to double, and with them the wait for the
+            // coefficients, behind the barrier
+            asm volatile("" : "+v"(lc.c1), "+v"(lc.c2), "+v"(lc.c3), "+v"(lc.wall));
             auto update = [&](const uint4& l, T gi, T gib, const LinkCoefT<T>& c) {
                 const T fpi = F[l.w & 0xFFFFu], fpib = F[l.w >> 16];
                 const double v = p.c0 * (double)gi + c.c1 * (double)gib + c.c2 * (double)fpi +
