@@ -100,13 +100,6 @@ __device__ __forceinline__ void link_gradient(const LinkGrad& lg, uint32_t k, do
     lg.g[k] += ak * (d1 * (double)fib + d2 * (double)fpi + d3 * (double)fpib);
     lg.g[lg.L1 + k] += ak * ws;
 }
-// The same with the three forward values read from the link runs of a step
-// record (fib at lk[k], f'_i at lk[L1 + k], f'_ibar at lk[2 L1 + k]).
-template <class T>
-__device__ __forceinline__ void link_gradient_rec(const LinkGrad& lg, const T* __restrict__ lk,
-                                                  uint32_t k, double ak, double ws) {
-    link_gradient(lg, k, ak, lk[k], lk[lg.L1 + k], lk[2 * lg.L1 + k], ws);
-}
 
 // Lattice data of a direction known only at run time (link lanes): e_d, w_d
 // and the opposite direction.
@@ -272,11 +265,18 @@ __device__ __forceinline__ NodePos node_of_wave(const Grid& g, const WaveList& w
 // a_k and the forward step's stored f'_i(y, t), f'_ibar(y, t) the link
 // lanes add the link's gradient sums.
 // UM: the forward state enters the collision adjoint only through its
-// velocity (the equilibrium's Jacobian depends on u alone), so with the rate
+// velocity (the equilibrium's Jacobian depends on u alone and is applied to
+// moments, which the transform back needs anyway), so with the rate
 // gradients off the kernel reads u(y, t) recorded by the forward step (D
 // planes of U) instead of pulling the Q populations of f(y, t), and the
 // link values of the gradients come from the same step record: A, wa and
 // nxt are not read.
+// Bound by HBM traffic and the mixed waves' latencies on large domains, by the
+// length of a launch on small ones.  The transforms by row factors, the
+// Jacobian on moments, the rate sums without divisions and wave_sums by halves
+// took a reverse step (node and link kernels, us) from 615 to 518 at 256^3 FP32
+// on records, 287 to 262 at 256x256x64 FP64, 750 to 604 at 256x256x128 FP32 with
+// the rate gradients and 85 to 72 at 96x64x64 FP64 with them and the replay.
 // Waves per SIMD asked of the compiler, where it stops just short of them:
 // FP64 on step records 4 (130 VGPRs fitted into 128 made the reverse step 3.5%
 // faster at 256^3); with the rate gradients FP64 D3 3, FP32 D3 4 and FP32 D2 6.

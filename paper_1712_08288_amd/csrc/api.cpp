@@ -152,16 +152,14 @@ int ensure_scratch(lbm_t* h, int64_t n_doubles) {
 }
 
 // Pinned host memory of the handle that kernels write results to, allocated on
-// first use and kept.
+// first use and kept; null where there is none to be had.
 constexpr int64_t kPinBytes = 1 << 20;
-int ensure_pinned(lbm_t* h) {
-    Engine& e = h->e;
-    if (e.pinned) return LBM_OK;
-    if (hipHostMalloc((void**)&e.pinned, kPinBytes, hipHostMallocDefault) != hipSuccess) {
+double* pinned(Engine& e) {
+    if (!e.pinned && hipHostMalloc((void**)&e.pinned, kPinBytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
         e.pinned = nullptr;
-        return fail(h, LBM_ENOMEM, "pinned host allocation failed");
     }
-    return LBM_OK;
+    return e.pinned;
 }
 
 template <class T>
@@ -374,9 +372,14 @@ int set_tiles(lbm_t* h, const int (*vel)[3]) {
     const size_t nl = links.link.size();
     links.link.resize(nl + (links.first.size() + 3) / 4);
     std::memcpy(links.link.data() + nl, links.first.data(), links.first.size() * 4);
-    if ((rc = upload(h, e.d_tile_link, reinterpret_cast<const uint4*>(links.link.data()),
-                     links.link.size())))
-        return rc;
+    rc = upload(h, e.d_tile_link, reinterpret_cast<const uint4*>(links.link.data()),
+                links.link.size());
+    if (rc == LBM_ENOMEM) {   // single steps need no table
+        (void)hipGetLastError();
+        e.tiles = lbe::TilePlan{};
+        return LBM_OK;
+    }
+    if (rc) return rc;
     e.d_tile_first = reinterpret_cast<const uint32_t*>(e.d_tile_link + nl);
     return sync(h);   // the upload reads `links`
 }
@@ -1023,8 +1026,7 @@ int lbm_moments(lbm_t* h, double* rho, double* u) {
     // Fields of a small domain go straight to pinned host memory: the kernel's
     // writes cost less than the copies (65x65 FP64: a call takes 21 us, 67 by
     // way of device memory).  Larger ones are left to the copy engine.
-    if (need * 8 <= kPinBytes) {
-        if ((rc = ensure_pinned(h))) return rc;
+    if (need * 8 <= kPinBytes && pinned(e)) {
         double* p_u = e.pinned + e.N;
         HIPCHK(h, lbe::launch_observe(e, e.buf[e.cur], e.pinned, p_u, nullptr));
         if ((rc = sync(h))) return rc;

@@ -204,7 +204,8 @@ inline constexpr Derived<L> DER{};
 // q_x are e_x, p_xx and pi_xx are 3 e_x^2 - |e|^2 -- so that a transform sums
 // each distinct pattern once per class and combines the sums, and back.  The
 // collision takes 199 floating-point instructions per D3Q19 node so, 245 with
-// every row summed on its own (D3Q15 152 and 175, D2Q9 78 and 85).
+// every row summed on its own (D3Q15 152 and 175, D2Q9 78 and 85); a step on
+// tiles, bound by the issue of these, 27.4 -> 25.9 us at 2048x2048 FP32.
 // Rows whose entries are parallel in every class form a group; v holds the
 // group's pattern on the pairs (coprime within a class) and c the factor of
 // row and class, M[k][i] = c[k][class] v[group][pair].

@@ -15,8 +15,8 @@
 // collisions and the load of the region (large domains: two blocks per CU, one
 // loads while the other computes) or a chain of LDS and arithmetic latencies
 // with three barriers, 0.6 to 0.9 us per step (small ones).  Single steps and
-// tiles, us per step: D2Q9 FP64 64x64 4.7 and 1.25, 1024x512 16.7 and 7.5,
-// 1999x1501 71 and 38; FP32 2048x2048 50.2 and 26.5; D3Q15 FP64 2x44x44 5.9
+// tiles, us per step: D2Q9 FP64 64x64 4.7 and 1.3, 1024x512 16.7 and 7.7,
+// 1999x1501 71 and 35; FP32 2048x2048 50.2 and 25.9; D3Q15 FP64 2x44x44 5.9
 // and 2.1.  A three-dimensional halo costs more than it saves on domains that
 // are not thin: 48^3 D3Q19 FP32 8.5 in single steps, 8.8 in tiles of 6^3 and
 // two steps.
@@ -120,7 +120,7 @@ k_tile_steps(const T* __restrict__ A, const T* __restrict__ waA, TileOut<T> out,
     // ---- load: the links this thread carries, its nodes' words and populations
     // The hardware deals blocks to the eight XCDs in turn; each takes the tiles
     // of one stretch, so that neighbours' halos are met in its own L2
-    // (1999x1501 FP64 38.1 -> 36.1 us per step, 1024x512 8.2 -> 7.5).
+    // (1999x1501 FP64 5% and 1024x512 8% less time per step).
     const uint32_t block = (blockIdx.x & 7u) * a.per_xcd + (blockIdx.x >> 3);
     if (block >= a.blocks) return;
     const uint32_t l0 = a.first[block], n_links = a.first[block + 1] - l0;
