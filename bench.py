@@ -35,7 +35,7 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per k_step<D3Q19, float> launch on this workload from rocprofv3
 # FETCH_SIZE/WRITE_SIZE (scaled by a copy of known size), valid for the
 # kernel sources with this hash (profiles/k_step_d3q19_fp32_spheres256.md).
-MEASURED_TRAFFIC = {"sources_sha256_16": "1672476243682091", "bytes": 2600527467}
+MEASURED_TRAFFIC = {"sources_sha256_16": "5370a5ad515c8f66", "bytes": 2600526889}
 KERNEL_SOURCES = ["paper_1712_08288_amd/csrc/forward.hip",
                   "paper_1712_08288_amd/csrc/kernels.hpp",
                   "paper_1712_08288_amd/csrc/lattice.hpp"]
@@ -339,9 +339,13 @@ def per_config_forward(binding, torch, windows=3):
             if rev:
                 res[prec]["adjoint_every_step_recorded"] = rev
         if name.startswith("c1"):
-            res["note"] = "0.6 MB working set, graph replay: launch-bound, not an HBM measurement"
+            res["note"] = "0.6 MB working set, several steps per launch: latency-bound, not an HBM measurement"
+        if name.startswith("c2"):
+            res["note"] = ("several steps per launch: the fractions count a single step's bytes, "
+                           "most of which stay on chip")
         if name.startswith("c4"):
-            res["note"] = "19-38 MB working set: runs partly from the 256 MB last-level cache"
+            res["note"] = ("19-38 MB working set, runs partly from the 256 MB last-level cache; "
+                           "several steps per launch")
         if name.startswith("c3_shard"):
             res["note"] = ("one of eight z-slabs of the 256^3 packing at its real shape "
                            "(independent packing of the same density, periodic in z)")
