@@ -830,7 +830,15 @@ int lbm_set_geometry(lbm_t* h, const uint8_t* solid, int64_t n_links,
         d8[k] = (uint8_t)e.lk_dir_h[k];
         n32[k] = (int32_t)e.lk_node_h[k];
     }
+    // From here on nothing of the previous geometry may be launched, also when
+    // the new one is refused further down: its tables are replaced one by one.
     e.has_geometry = false;
+    e.initialized = false;
+    e.stepped = false;
+    e.have_grad = false;
+    e.adj_started = false;
+    e.tiles = lbe::TilePlan{};
+    e.d_tile_first = nullptr;
     drop_graphs(e);
     free_run(e);
     int rc;
@@ -858,9 +866,6 @@ int lbm_set_geometry(lbm_t* h, const uint8_t* solid, int64_t n_links,
     }
     if ((rc = set_tiles(h, E))) return rc;
     e.has_geometry = true;
-    e.initialized = false;
-    e.have_grad = false;
-    e.adj_started = false;
     return sync(h);
 }
 
