@@ -1192,7 +1192,7 @@ int lbm_set_objective(lbm_t* h, int kind, int32_t tag, int64_t t_begin, int64_t 
     e.obj_tag = tag;
     e.obj_t0 = t_begin;
     e.obj_t1 = t_end;
-    const int64_t len = kind == LBM_OBJ_FORCE_X ? e.n_links : lbe::step_blocks(e);
+    const int64_t len = kind == LBM_OBJ_FORCE_X ? e.n_links + 1 : lbe::step_blocks(e);
     if (kind == LBM_OBJ_NONE || e.obj_acc_len != len) free_dev(e.d_obj_acc);
     e.obj_acc_len = 0;
     if (kind != LBM_OBJ_NONE) {
@@ -1246,15 +1246,20 @@ int lbm_objective(lbm_t* h, double* J) {
     Engine& e = h->e;
     *J = 0.0;
     if (e.obj_kind == LBM_OBJ_NONE || e.obj_acc_len == 0) return LBM_OK;
-    const bool links = e.obj_kind == LBM_OBJ_FORCE_X;
-    int rc = ensure_scratch(h, 1 + (links ? lbe::link_blocks(e) : 0));
+    const bool drag = e.obj_kind == LBM_OBJ_FORCE_X;
+    int rc = ensure_scratch(h, 4 + (drag ? 4 * lbe::link_blocks(e) : 0));
     if (rc) return rc;
-    if (links)
-        HIPCHK(h, lbe::launch_sum_links(e, e.d_obj_acc, e.d_scratch + 1, e.d_scratch));
+    if (drag)
+        HIPCHK(h, lbe::launch_drag_sums(e, e.d_obj_acc, e.obj_tag, e.d_scratch + 4, e.d_scratch));
     else
         HIPCHK(h, lbe::launch_sum_blocks(e, e.d_obj_acc, e.obj_acc_len, 1, e.d_scratch));
-    HIPCHK(h, hipMemcpyAsync(J, e.d_scratch, 8, hipMemcpyDeviceToHost, e.stream));
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    HIPCHK(h, hipMemcpyAsync(sum, e.d_scratch, drag ? 32 : 8, hipMemcpyDeviceToHost, e.stream));
     if ((rc = sync(h))) return rc;
+    // the constant part of the force, 2 w_i rho0 e_ibar,x on every link and step
+    const double constant = 2.0 * e.rho0 * (lat_w(e.lattice, 1) * sum[1] +
+                                            lat_w(e.lattice, e.Q - 1) * sum[2]);
+    *J = sum[0] + constant * (sum[3] / (double)(e.obj_t1 - e.obj_t0));
     if (!std::isfinite(*J)) return fail(h, LBM_ENONFINITE, "objective is not finite");
     return LBM_OK;
 }

@@ -124,7 +124,7 @@ struct Engine {
     int64_t obj_x_in = 0, obj_x_out = -1;   // pressure-drop planes (-1: nx - 1)
     double obj_a_in = 0.0, obj_a_out = 0.0; // 1 / (fluid nodes of each plane)
     std::vector<int64_t> fluid_per_x;       // fluid nodes of each plane x = const
-    double* d_obj_acc = nullptr;        // partial sums: per link (drag) or per block
+    double* d_obj_acc = nullptr;        // partial sums: per link and the steps (drag) or per block
     int64_t obj_acc_len = 0;
 
     // checkpointed run and adjoint
@@ -245,11 +245,14 @@ hipError_t launch_plane_density(Engine& e, const Snapshot& in, uint32_t x_in, ui
 // per-block partial momentum-exchange force: (nblocks, n_tags, D)
 hipError_t launch_force(Engine& e, const Snapshot& post, double* partials,
                         int64_t* nblocks);
-// acc[k] += weight times the x force on link k, for the links of one tag
+// acc[k] += weight times the x force of link k's deviations, for the links of
+// one tag; the step is counted in acc[n_links] (a 64-bit integer)
 hipError_t launch_force_objective(Engine& e, const Snapshot& post, double* acc,
                                   int tag, double weight);
-// out[0] = sum of n values in a fixed order; partials: link_blocks(e) doubles
-hipError_t launch_sum_links(Engine& e, const double* v, double* partials, double* out);
+// out: the sum of acc in a fixed order, -e_ix summed over the tag's axis links
+// and over its diagonal links, the steps counted; partials: 4 link_blocks(e)
+// doubles
+hipError_t launch_drag_sums(Engine& e, const double* acc, int tag, double* partials, double* out);
 // LBM_DEBUG: fill n values of T (the handle's precision) at p with NaN
 hipError_t launch_fill_nan(Engine& e, void* p, size_t n);
 // out[c] = sum_b partials[b*cols + c], deterministic
@@ -276,9 +279,10 @@ hipError_t launch_link_coefficients(Engine& e);
 TileLimits tile_limits(const Engine& e);
 // once per plan, with the handle's device current
 hipError_t tile_setup(const Engine& e);
-// drag of the launch's steps s0 <= s < s1: weight times the x force on link k
-// is added to acc[k] for the links of one tag (acc null: none; not with
-// Eq. (211), whose link values the last step does not complete)
+// drag of the launch's steps s0 <= s < s1: weight times the x force of link k's
+// deviations is added to acc[k] for the links of one tag and s1 - s0 to the
+// step count acc[n_links] (acc null: none; not with Eq. (211), whose link
+// values the last step does not complete)
 struct TileDrag {
     double* acc = nullptr;
     int tag = 0, s0 = 0, s1 = 0;

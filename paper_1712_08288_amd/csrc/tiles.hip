@@ -64,6 +64,7 @@ struct TileArgs {
     // drag of the steps s with s0 <= s < s1 (TileDrag)
     double* acc;
     const int32_t* lktag;
+    uint32_t n_all;     // links of the domain: the step count's place in acc
     int tag, s0, s1;
     double weight;
     double ws[kTileSteps];   // factor on the wall terms of each step
@@ -123,6 +124,9 @@ k_tile_steps(const T* __restrict__ A, const T* __restrict__ waA, TileOut<T> out,
     // (1999x1501 FP64 5% and 1024x512 8% less time per step).
     const uint32_t block = (blockIdx.x & 7u) * a.per_xcd + (blockIdx.x >> 3);
     if (block >= a.blocks) return;
+    if (a.acc && block == 0 && t == 0)
+        (void)atomicAdd(reinterpret_cast<unsigned long long*>(a.acc) + a.n_all,   // not waited for
+                        (unsigned long long)(a.s1 - a.s0));
     const uint32_t l0 = a.first[block], n_links = a.first[block + 1] - l0;
     const bool has_link = (uint32_t)t < n_links, has_more = (uint32_t)(t + NT) < n_links;
     const uint4 lk = has_link ? a.link[l0 + (uint32_t)t] : uint4{0u, 0u, 0u, 0u};
@@ -335,8 +339,7 @@ k_tile_steps(const T* __restrict__ A, const T* __restrict__ waA, TileOut<T> out,
                 F[l.z & 0xFFFFu] = next;
                 if (in_drag && s >= a.s0 && s < a.s1) {
                     const int ex = (int)((l.x >> 7) & 3u) - 1;
-                    const double w2 = 2.0 * ((l.x >> 6) & 1u ? L::W[1] : L::W[Q - 1]);
-                    sum += a.weight * (-(double)ex * ((double)fpib + (double)next + w2 * p.rho0_d));
+                    sum += a.weight * (-(double)ex * ((double)fpib + (double)next));
                 }
             };
             if ((int)(lk.x & 31u) >= need) update(lk, fi, fib, lc, drag_own, drag);
@@ -412,6 +415,7 @@ hipError_t launch_tile_steps(Engine& e, const Snapshot& in, const Snapshot* cons
     a.steps = steps;
     a.acc = drag.acc;
     a.lktag = e.d_lktag;
+    a.n_all = (uint32_t)e.n_links;
     a.tag = drag.tag;
     a.s0 = drag.s0;
     a.s1 = drag.s1;
