@@ -348,6 +348,8 @@ class Solver:
                 ptr.append(_p(v.data_ptr()))
             else:
                 v = _f64(v)
+                if v is not None and v.size < n:
+                    raise ValueError("update_links: expected %d values, got %d" % (n, v.size))
                 ptr.append(v)
         self._chk(_update_links(self._h, *(_ptr(v) if isinstance(v, np.ndarray) else v for v in ptr)),
                   "update_links")

@@ -1,0 +1,33 @@
+"""Solver.update_links' checks of its arguments (no GPU: the library call and the
+handle's counts are replaced)."""
+
+import numpy as np
+import pytest
+
+L, D = 6, 2
+
+
+@pytest.fixture
+def solver(monkeypatch):
+    from paper_1712_08288_amd import binding
+    calls = []
+    monkeypatch.setattr(binding, "_update_links", lambda h, q, u: calls.append((q, u)) or 0)
+    monkeypatch.setattr(binding.Solver, "counts", lambda self: (40, L))
+    sv = binding.Solver.__new__(binding.Solver)
+    sv._h, sv.D = None, D
+    sv.calls = calls
+    return sv
+
+
+def test_short_host_arrays_are_refused(solver):
+    """The library reads L and L D values: no further than the array goes."""
+    for kw in (dict(q=np.ones(L - 1)), dict(q=[]), dict(wall_u=np.zeros((L - 1, D))),
+               dict(q=np.ones(L), wall_u=np.zeros(L))):
+        with pytest.raises(ValueError):
+            solver.update_links(**kw)
+    assert not solver.calls
+    solver.update_links(np.ones(L), np.zeros((L, D)))
+    solver.update_links([0.5] * L)
+    solver.update_links(np.ones(L + 3))      # what lies behind is not read
+    solver.update_links()
+    assert len(solver.calls) == 4 and solver.calls[3] == (None, None)
