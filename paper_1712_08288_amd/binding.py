@@ -342,7 +342,7 @@ class Solver:
         ptr = []
         for v, n in ((q, nl), (wall_u, nl * self.D)):
             if hasattr(v, "is_cuda") and v.is_cuda:
-                if v.numel() != n or not v.is_contiguous() or str(v.dtype) != "torch.float64":
+                if v.numel() < n or not v.is_contiguous() or str(v.dtype) != "torch.float64":
                     raise ValueError("update_links: expected a contiguous float64 device tensor "
                                      "of %d values" % n)
                 ptr.append(_p(v.data_ptr()))
