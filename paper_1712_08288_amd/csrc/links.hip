@@ -9,8 +9,10 @@
 
 namespace lbe {
 
-// the free parameter l(gamma) (paper, Section 3 and Eq. (212)) and dl/dgamma
+// the free parameter l(gamma) (paper, Section 3 and Eq. (212)) and dl/dgamma,
+// rounded operation by operation like the coefficients made from them
 __device__ __forceinline__ double l_of(int rule, double g) {
+#pragma clang fp contract(off)
     switch (rule) {
         case 0: return g;
         case 1: return 1.5 * g;
@@ -22,6 +24,7 @@ __device__ __forceinline__ double l_of(int rule, double g) {
     }
 }
 __device__ __forceinline__ double dl_of(int rule, double g) {
+#pragma clang fp contract(off)
     switch (rule) {
         case 0: return 1.0;
         case 1: return 1.5;
