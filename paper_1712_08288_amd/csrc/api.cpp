@@ -15,6 +15,7 @@
 #include "engine.hpp"
 #include "geometry.hpp"
 #include "lattice.hpp"
+#include "link_rule.hpp"
 
 using lbe::Engine;
 using lbe::Snapshot;
@@ -216,10 +217,32 @@ int alloc_links(lbm_t* h) {
     return LBM_OK;
 }
 
-// Take gamma and phi (host or device; in the caller's order, or in link order
-// when `sorted`; null: unchanged), check them and make the link tables; the
-// old values stay when a value is refused.
-int take_links(lbm_t* h, const double* q, const double* wall_u, bool sorted) {
+int refuse_gamma(lbm_t* h, int64_t k, double g) {
+    return fail(h, LBM_EINVAL,
+                "l(gamma) outside the convex band max(0,2g-1) <= l <= 2g at link " +
+                    std::to_string(h->e.perm[k]) + " (gamma = " + std::to_string(g) + ")");
+}
+
+// The link tables of a new geometry, from its gamma (in (0, 1]) and phi in link
+// order, which stay until the stream is waited for.  Checked on the host, where
+// these values are anyway: the device's check costs a kernel, its answer and a
+// wait (8x8x8 D3Q15, where little else is done: lbm_set_geometry 182 -> 141 us).
+int first_links(lbm_t* h, const std::vector<double>& q, const std::vector<double>& wall_u) {
+    Engine& e = h->e;
+    for (size_t k = 0; k < q.size(); ++k)
+        if (!lbe::l_convex(e.l_rule, q[k])) return refuse_gamma(h, (int64_t)k, q[k]);
+    if (q.empty()) return LBM_OK;
+    HIPCHK(h, hipMemcpyAsync(e.d_q, q.data(), q.size() * 8, hipMemcpyHostToDevice, e.stream));
+    HIPCHK(h, hipMemcpyAsync(e.d_wall_u, wall_u.data(), wall_u.size() * 8, hipMemcpyHostToDevice,
+                             e.stream));
+    HIPCHK(h, lbe::launch_link_coefficients(e));
+    return LBM_OK;
+}
+
+// Take gamma and phi (host or device, in the caller's order; null: unchanged),
+// check them and make the link tables; the old values stay when a value is
+// refused.
+int take_links(lbm_t* h, const double* q, const double* wall_u) {
     Engine& e = h->e;
     const size_t L = (size_t)e.n_links;
     if (L == 0) return LBM_OK;
@@ -232,8 +255,7 @@ int take_links(lbm_t* h, const double* q, const double* wall_u, bool sorted) {
     if (q) HIPCHK(h, hipMemcpyAsync(q_dev, q, L * 8, hipMemcpyDefault, e.stream));
     if (wall_u)
         HIPCHK(h, hipMemcpyAsync(wall_dev, wall_u, L * (size_t)e.D * 8, hipMemcpyDefault, e.stream));
-    HIPCHK(h, lbe::launch_take_links(e, q ? q_dev : nullptr, wall_u ? wall_dev : nullptr,
-                                     sorted ? nullptr : e.d_perm, bad_dev));
+    HIPCHK(h, lbe::launch_take_links(e, q ? q_dev : nullptr, wall_u ? wall_dev : nullptr, bad_dev));
     uint32_t bad[2] = {0u, 0u};
     HIPCHK(h, hipMemcpyAsync(bad, bad_dev, 8, hipMemcpyDeviceToHost, e.stream));
     if ((rc = sync(h))) return rc;
@@ -242,9 +264,7 @@ int take_links(lbm_t* h, const double* q, const double* wall_u, bool sorted) {
         double g = 0.0;
         HIPCHK(h, hipMemcpyAsync(&g, e.d_q_next + bad[1], 8, hipMemcpyDeviceToHost, e.stream));
         if ((rc = sync(h))) return rc;
-        return fail(h, LBM_EINVAL,
-                    "l(gamma) outside the convex band max(0,2g-1) <= l <= 2g at link " +
-                        std::to_string(e.perm[bad[1]]) + " (gamma = " + std::to_string(g) + ")");
+        return refuse_gamma(h, bad[1], g);
     }
     std::swap(e.d_q, e.d_q_next);
     std::swap(e.d_wall_u, e.d_wall_u_next);
@@ -351,12 +371,12 @@ int forward_step(lbm_t* h, const Snapshot& in, const Snapshot& out, bool accumul
 }
 
 // Tiles for launches of several steps: the best plan whose regions hold their
-// links, none where single steps are expected to be as fast.
-int set_tiles(lbm_t* h, const int (*vel)[3]) {
+// links, none where single steps are expected to be as fast.  `links` stays
+// until the stream is waited for.
+int set_tiles(lbm_t* h, const int (*vel)[3], lbe::TileLinks& links) {
     Engine& e = h->e;
     const int64_t n[3] = {e.nx, e.ny, e.nz};
     const lbe::TileLimits lim = lbe::tile_limits(e);
-    lbe::TileLinks links;
     e.tiles = lbe::TilePlan{};
     for (const lbe::TilePlan& p : lbe::tile_plans(n, lim, e.Q, e.D, (int)e.elem))
         if (lbe::tile_links(p, n, lim, e.Q, vel, e.lk_node_h, e.lk_dir_h, e.ibar_is_link,
@@ -381,7 +401,7 @@ int set_tiles(lbm_t* h, const int (*vel)[3]) {
     }
     if (rc) return rc;
     e.d_tile_first = reinterpret_cast<const uint32_t*>(e.d_tile_link + nl);
-    return sync(h);   // the upload reads `links`
+    return LBM_OK;
 }
 
 // How many of the next `left` steps from time t one launch on tiles may take
@@ -855,7 +875,7 @@ int lbm_set_geometry(lbm_t* h, const uint8_t* solid, int64_t n_links,
     if ((rc = upload(h, e.d_lktag, e.tag_h.data(), e.tag_h.size()))) return rc;
     if ((rc = upload(h, e.d_lkibar, e.ibar_is_link.data(), e.ibar_is_link.size()))) return rc;
     if ((rc = alloc_links(h))) return rc;
-    if ((rc = take_links(h, tab.q.data(), tab.wall_u.data(), true))) return rc;
+    if ((rc = first_links(h, tab.q, tab.wall_u))) return rc;
     for (auto& b : e.buf) {
         if (b.wa) (void)hipFree(b.wa);
         if (hipMalloc(&b.wa, wa_bytes(e)) != hipSuccess) {
@@ -864,7 +884,8 @@ int lbm_set_geometry(lbm_t* h, const uint8_t* solid, int64_t n_links,
         }
         if ((rc = zero(h, b.wa, wa_bytes(e)))) return rc;
     }
-    if ((rc = set_tiles(h, E))) return rc;
+    lbe::TileLinks tile_links;
+    if ((rc = set_tiles(h, E, tile_links))) return rc;
     e.has_geometry = true;
     return sync(h);
 }
@@ -875,7 +896,7 @@ int lbm_update_links(lbm_t* h, const double* q, const double* wall_u) {
     if (!e.has_geometry) return fail(h, LBM_ESTATE, "no geometry");
     HIPCHK(h, hipStreamSynchronize(e.stream));
     drop_graphs(e);
-    return take_links(h, q, wall_u, false);
+    return take_links(h, q, wall_u);
 }
 
 int lbm_set_parameters(lbm_t* h, const double* s, const double* g) {

@@ -266,11 +266,10 @@ int64_t adjoint_blocks(const Engine& e);    // blocks of the two adjoint launche
 int64_t link_blocks(const Engine& e);       // blocks of a link launch
 
 // ---- launchers (links.hip) ----------------------------------------------------
-// gamma and phi (device, caller's order, or link order with perm null; null:
-// unchanged) into d_q_next and d_wall_u_next.  bad[0], bad[1] (set to all ones
-// before): the first link whose gamma, or whose l(gamma), is out of range.
-hipError_t launch_take_links(Engine& e, const double* q, const double* wall_u, const int32_t* perm,
-                             uint32_t* bad);
+// gamma and phi (device, caller's order; null: unchanged) into d_q_next and
+// d_wall_u_next.  bad[0], bad[1] (set to all ones before): the first link whose
+// gamma, or whose l(gamma), is out of range.
+hipError_t launch_take_links(Engine& e, const double* q, const double* wall_u, uint32_t* bad);
 // the link tables from d_q and d_wall_u
 hipError_t launch_link_coefficients(Engine& e);
 

@@ -5,40 +5,13 @@
 // through the autograd function, new link fractions each time: 12.6 -> 5.7 ms).
 #include "engine.hpp"
 #include "kernels.hpp"
+#include "link_rule.hpp"
 #include "params.hpp"
 
 namespace lbe {
 
-// the free parameter l(gamma) (paper, Section 3 and Eq. (212)) and dl/dgamma,
-// rounded operation by operation like the coefficients made from them
-__device__ __forceinline__ double l_of(int rule, double g) {
-#pragma clang fp contract(off)
-    switch (rule) {
-        case 0: return g;
-        case 1: return 1.5 * g;
-        case 2: return 2.0 * g;
-        case 3: return g * g;
-        case 4: return g * g + g;
-        case 5: return 0.0;
-        default: return 2.0 * g - 1.0 > 0.0 ? 2.0 * g - 1.0 : 0.0;
-    }
-}
-__device__ __forceinline__ double dl_of(int rule, double g) {
-#pragma clang fp contract(off)
-    switch (rule) {
-        case 0: return 1.0;
-        case 1: return 1.5;
-        case 2: return 2.0;
-        case 3: return 2.0 * g;
-        case 4: return 2.0 * g + 1.0;
-        case 5: return 0.0;
-        default: return 2.0 * g - 1.0 > 0.0 ? 2.0 : 0.0;
-    }
-}
-
-// One thread per link: its gamma and phi from the caller's order (perm; null:
-// already in link order) into q and wall_u (q_in or wall_in null: the values
-// they had).  bad[0], bad[1]: the first link whose gamma is outside (0, 1] or
+// One thread per link: its gamma and phi from the caller's order (perm) into q
+// and wall_u (q_in or wall_in null: the values they had).  bad[0], bad[1]: the first link whose gamma is outside (0, 1] or
 // whose l(gamma) is outside the band of Eq. (212).
 template <int D>
 __global__ void __launch_bounds__(BX)
@@ -48,7 +21,7 @@ k_take_links(const double* __restrict__ q_in, const double* __restrict__ wall_in
              double* __restrict__ wall_u, uint32_t* __restrict__ bad) {
     const uint32_t k = blockIdx.x * BX + threadIdx.x;
     if (k >= L) return;
-    const size_t pk = perm ? (size_t)(uint32_t)perm[k] : (size_t)k;
+    const size_t pk = (size_t)(uint32_t)perm[k];
     const double g = q_in ? q_in[pk] : q_old[k];
     q[k] = g;
     for (int a = 0; a < D; ++a)
@@ -57,8 +30,7 @@ k_take_links(const double* __restrict__ q_in, const double* __restrict__ wall_in
         atomicMin(&bad[0], k);
         return;
     }
-    const double l = l_of(rule, g), lo = fmax(0.0, 2.0 * g - 1.0);
-    if (!(l >= lo - 1e-12 && l <= 2.0 * g + 1e-12)) atomicMin(&bad[1], k);
+    if (!l_convex(rule, g)) atomicMin(&bad[1], k);
 }
 
 // Coefficients of Eq. (213) for every link and their gamma derivatives along
@@ -107,11 +79,10 @@ k_link_coefficients(const double* __restrict__ q, const double* __restrict__ wal
     c4v[k] = c4;
 }
 
-hipError_t launch_take_links(Engine& e, const double* q, const double* wall_u, const int32_t* perm,
-                             uint32_t* bad) {
+hipError_t launch_take_links(Engine& e, const double* q, const double* wall_u, uint32_t* bad) {
     if (!e.n_links) return hipSuccess;
     auto kern = e.D == 2 ? k_take_links<2> : k_take_links<3>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)link_blocks(e)), dim3(BX), 0, e.stream, q, wall_u, perm,
+    hipLaunchKernelGGL(kern, dim3((unsigned)link_blocks(e)), dim3(BX), 0, e.stream, q, wall_u, e.d_perm,
                        e.d_q, e.d_wall_u, e.l_rule, (uint32_t)e.n_links, e.d_q_next,
                        e.d_wall_u_next, bad);
     return hipGetLastError();

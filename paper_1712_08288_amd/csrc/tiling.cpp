@@ -27,165 +27,227 @@ namespace {
 
 // Microseconds that a launch of plan p takes on 256 CUs, to compare plans by.
 // Fitted to D2Q9 launches of 2..12 steps on 64 x 64 to 2048 x 2048 nodes.
-constexpr double kCus = 256, kBytesPerUs = 6.2e6;
+constexpr double kCus = 256, kBytesPerUs = 6.2e6, kLaunch = 3.0, kChain = 0.62;
 
-double launch_us(const TilePlan& p, const TileLimits& lim, int Q, int elem) {
-    double region = 1, tile = 1, computed = 0;
-    for (int a = 0; a < 3; ++a) {
-        region *= p.region[a];
-        tile *= p.tile[a];
-    }
-    // nodes of the waves that compute in some step: waves run along x
-    for (int s = 1; s <= p.halo; ++s) {
-        double c = p.region[0];
-        for (int a = 1; a < 3; ++a) c *= p.region[a] - ((p.wrap >> a) & 1u ? 0 : 2 * s);
-        computed += c;
-    }
+// In two parts, without and with the bytes moved: the first alone rules most
+// plans out (a search takes 5 to 40 us, a tenth of what it took with every
+// estimate made in full and all plans sorted; lbm_set_geometry 80x42 FP64
+// 398 -> 312 us, 301 without tiles).
+struct LaunchTime {
+    double rounds, at_once, compute;   // compute: microseconds of the steps
+};
+
+// What a tile size and a halo make of one direction.
+struct Axis {
+    int tile, region, ntile;
+    bool wrap;
+    double line;   // bytes moved for each byte of a row of these tiles
+};
+
+LaunchTime launch_steps(const Axis& x, const Axis& y, const Axis& z, int halo, double blocks, int per_cu,
+                        double node, int elem) {
+    const double X = x.region, Y = y.region, Z = z.region, h = halo;
+    // nodes of the waves that compute in some step (waves run along x), the sum
+    // of X (Y - 2s or Y) (Z - 2s or Z) over s = 1 .. h
+    const double y2 = y.wrap ? 0 : 2, z2 = z.wrap ? 0 : 2;
+    const double computed = X * (h * Y * Z - (y2 * Z + z2 * Y) * h * (h + 1) * 0.5 +
+                                 y2 * z2 * h * (h + 1) * (2 * h + 1) * (1.0 / 6));
     const double waves = computed / (64 * 4);   // on each SIMD
-    const double node = Q == 9 ? 1.0 : Q == 15 ? 1.9 : 2.5;
-    const double sharing = std::min<double>(lim.per_cu, std::max(1.0, p.blocks / kCus));
-    const double rounds = std::max(1.0, p.blocks / (kCus * lim.per_cu));
-    // rows are read and written in 64-byte lines that their ends share
-    const double line = 1 + 32.0 / (p.tile[0] * elem);
-    const double at_once = std::min<double>(p.blocks, kCus * lim.per_cu);
-    const double move = at_once * (region + tile) * Q * elem * line / kBytesPerUs;
+    const double sharing = std::min<double>(per_cu, std::max(1.0, blocks / kCus));
+    const double full = per_cu == 2 ? blocks / (2 * kCus) : blocks / kCus;
     // one block: a chain of LDS and arithmetic latencies; many: the rate at
     // which a SIMD issues the collisions
-    const double chain = p.halo * 0.62 + waves * node * (elem == 8 ? 0.2 : 0.1);
+    const double chain = h * kChain + waves * node * (elem == 8 ? 0.2 : 0.1);
     const double issue = waves * node * sharing * (elem == 8 ? 0.15 : 0.08);
-    return 3.0 + rounds * move + std::max(chain, rounds * issue);
+    LaunchTime t;
+    t.rounds = std::max(1.0, full);
+    t.at_once = std::min<double>(blocks, kCus * per_cu);
+    t.compute = std::max(chain, t.rounds * issue);
+    return t;
 }
 
 }  // namespace
 
 std::vector<TilePlan> tile_plans(const int64_t (&n)[3], const TileLimits& lim, int Q, int D, int elem) {
-    struct Rated {
-        double us;
-        TilePlan p;
-    };
-    std::vector<Rated> all;
+    constexpr size_t kBest = 8;
+    double us[kBest];
+    std::vector<TilePlan> best;
+    best.reserve(kBest);
     const double nodes = (double)n[0] * (double)n[1] * (double)n[2];
     const double single = std::max(4.0, 2.0 + 2.0 * Q * elem * nodes / kBytesPerUs);
+    const double node = Q == 9 ? 1.0 : Q == 15 ? 1.9 : 2.5;
     // Regions over 512 nodes in three dimensions lose more to the halo than a
     // launch costs, so on domains that are not thin no plan passes the test
     // against single steps below; it asks for a clear gain, because the figures
     // compared are estimates (measured: the chosen plan within 6% of the best
     // of those tried on 18 domains).
-    static const int halos[] = {2, 3, 4, 5, 6, 7, 8, 10, 12, 16};
+    double limit = 0.85 * single;
+    static const int halos[] = {16, 12, 10, 8, 7, 6, 5, 4, 3, 2};
     static const int sizes[] = {2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 28, 32, 40, 48, 56, 64};
-    for (const int halo : halos)
-        for (const int x : sizes) {
-            if (x + 2 * halo > lim.nodes) break;
-            for (const int y : sizes) {
-                if (std::min<int64_t>(n[0], x + 2 * halo) * std::min<int64_t>(n[1], y + 2 * halo) >
-                    lim.nodes)
-                    break;
-                for (const int z : sizes) {
-                    if (D == 2 && z != sizes[0]) break;
-                    const int tile[3] = {x, y, z};
-                    const TilePlan p = tile_plan(n, lim, tile, halo);
-                    if (!p.halo) break;
-                    const double us = launch_us(p, lim, Q, elem) / halo;
-                    if (us < 0.85 * single) all.push_back(Rated{us, p});
-                    if (p.wrap & 4u) break;   // larger tiles give the same plan
-                }
-                if (y + 2 * halo >= n[1]) break;
+    constexpr int kSizes = sizeof(sizes) / sizeof(sizes[0]);
+    for (const int halo : halos) {
+        const double per_step = 1.0 / halo;
+        if (kLaunch * per_step + kChain >= limit) continue;   // whatever the tile
+        // per direction the sizes up to the first that covers the period (larger
+        // ones make the same plans)
+        Axis axis[3][kSizes];
+        int count[3] = {0, 0, 0};
+        for (int a = 0; a < 3; ++a)
+            for (const int size : sizes) {
+                Axis& x = axis[a][count[a]++];
+                x.wrap = size + 2 * halo >= n[a];
+                x.tile = x.wrap ? (int)n[a] : size;
+                x.region = x.wrap ? (int)n[a] : size + 2 * halo;
+                x.ntile = x.wrap ? 1 : (int)((n[a] + size - 1) / size);
+                // rows are read and written in 64-byte lines that their ends share
+                x.line = a == 0 ? 1 + 32.0 / (x.tile * elem) : 1.0;
+                if (x.wrap || x.region > lim.nodes || (a == 2 && D == 2)) break;
             }
-            if (x + 2 * halo >= n[0]) break;
-        }
-    std::stable_sort(all.begin(), all.end(), [](const Rated& a, const Rated& b) { return a.us < b.us; });
-    std::vector<TilePlan> out;
-    for (const Rated& r : all) {
-        if (out.size() == 8) break;
-        out.push_back(r.p);
+        for (int i = 0; i < count[0] && axis[0][i].region <= lim.nodes; ++i)
+            for (int j = 0; j < count[1]; ++j) {
+                const Axis &x = axis[0][i], &y = axis[1][j];
+                if ((int64_t)x.region * y.region > lim.nodes) break;
+                for (int k = 0; k < count[2]; ++k) {
+                    const Axis& z = axis[2][k];
+                    const int64_t blocks = (int64_t)x.ntile * y.ntile * z.ntile;
+                    if ((int64_t)x.region * y.region * z.region > lim.nodes) break;
+                    if (std::max(std::max(x.ntile, y.ntile), z.ntile) > 65535 || blocks > (1LL << 24))
+                        continue;
+                    const LaunchTime t =
+                        launch_steps(x, y, z, halo, (double)blocks, lim.per_cu, node, elem);
+                    if ((kLaunch + t.compute) * per_step >= limit) continue;
+                    const double region = (double)x.region * y.region * z.region;
+                    const double tile = (double)x.tile * y.tile * z.tile;
+                    const double move =
+                        t.at_once * (region + tile) * Q * elem * x.line * (1.0 / kBytesPerUs);
+                    const double total = (kLaunch + t.rounds * move + t.compute) * per_step;
+                    if (total >= limit) continue;
+                    // into its place among the best, behind equal ones
+                    size_t r = best.size() == kBest ? kBest - 1 : best.size();
+                    if (r == best.size()) best.emplace_back();
+                    for (; r > 0 && total < us[r - 1]; --r) {
+                        us[r] = us[r - 1];
+                        best[r] = best[r - 1];
+                    }
+                    us[r] = total;
+                    TilePlan& p = best[r];
+                    p = TilePlan{};
+                    p.halo = halo;
+                    const Axis* at[3] = {&x, &y, &z};
+                    for (int a = 0; a < 3; ++a) {
+                        p.tile[a] = at[a]->tile;
+                        p.region[a] = at[a]->region;
+                        p.ntile[a] = at[a]->ntile;
+                        if (at[a]->wrap) p.wrap |= 1u << a;
+                    }
+                    p.blocks = (unsigned)blocks;
+                    if (best.size() == kBest) limit = us[kBest - 1];
+                }
+            }
     }
-    return out;
+    return best;
 }
 
 bool tile_links(const TilePlan& p, const int64_t (&n)[3], const TileLimits& lim, int Q,
                 const int (*e)[3], const std::vector<int64_t>& node, const std::vector<int8_t>& dir,
                 const std::vector<uint8_t>& ibar_link, bool pressure, bool outflow, TileLinks& out) {
     // per direction and coordinate, the tiles whose region's inside (all but
-    // its outermost layer) holds it, with the place in the region
+    // its outermost layer) holds it, with the place in the region, how far that
+    // is from the region's edge and whether it is the tile's own: those of
+    // coordinate x at [first[x], first[x + 1])
     struct On {
         int tile, loc;
+        uint32_t edge, mine;
     };
-    std::vector<std::vector<On>> on[3];
+    std::vector<On> on[3];
+    std::vector<uint32_t> first[3];
     for (int a = 0; a < 3; ++a) {
-        on[a].resize((size_t)n[a]);
-        const bool wrap = (p.wrap >> a) & 1u;
-        for (int j = 0; j < p.ntile[a]; ++j)
-            for (int loc = wrap ? 0 : 1; loc < p.region[a] - (wrap ? 0 : 1); ++loc) {
-                const int64_t u = (int64_t)j * p.tile[a] - (wrap ? 0 : p.halo) + loc;
-                on[a][(size_t)(((u % n[a]) + n[a]) % n[a])].push_back(On{j, loc});
-            }
+        const int wrap = (int)((p.wrap >> a) & 1u), edge = 1 - wrap;
+        auto each = [&](auto&& f) {
+            for (int j = 0; j < p.ntile[a]; ++j)
+                for (int loc = edge; loc < p.region[a] - edge; ++loc) {
+                    const int64_t u = (int64_t)j * p.tile[a] - (wrap ? 0 : p.halo) + loc;
+                    const bool mine = wrap || (loc >= p.halo && loc < p.halo + p.tile[a] && u < n[a]);
+                    f((size_t)(u < 0 ? u + n[a] : u >= n[a] ? u - n[a] : u),
+                      On{j, loc, wrap ? 31u : (uint32_t)std::min(loc, p.region[a] - 1 - loc), mine});
+                }
+        };
+        first[a].assign((size_t)n[a] + 2, 0u);
+        each([&](size_t u, On) { ++first[a][u + 2]; });
+        for (size_t u = 2; u < first[a].size(); ++u) first[a][u] += first[a][u - 1];
+        on[a].resize(first[a].back());
+        each([&](size_t u, On o) { on[a][first[a][u + 1]++] = o; });
     }
     std::vector<int> opp((size_t)Q, 0);
     for (int i = 0; i < Q; ++i)
         for (int j = 0; j < Q; ++j)
             if (e[j][0] == -e[i][0] && e[j][1] == -e[i][1] && e[j][2] == -e[i][2]) opp[i] = j;
     // every link's regions in turn, first to count and then to place
-    auto each = [&](auto&& f) {
-        for (size_t k = 0; k < node.size(); ++k) {
-            const int64_t x[3] = {node[k] % n[0], (node[k] / n[0]) % n[1], node[k] / (n[0] * n[1])};
-            for (const On& z : on[2][(size_t)x[2]])
-                for (const On& y : on[1][(size_t)x[1]])
-                    for (const On& xx : on[0][(size_t)x[0]]) {
-                        const On at[3] = {xx, y, z};
-                        f(k, x,
-                          (size_t)xx.tile + (size_t)p.ntile[0] *
-                                                ((size_t)y.tile + (size_t)p.ntile[1] * (size_t)z.tile),
-                          at);
-                    }
-        }
+    const uint32_t nx = (uint32_t)n[0], ny = (uint32_t)n[1];
+    auto each = [&](size_t k, uint32_t (&x)[3], auto&& f) {
+        const uint32_t yz = (uint32_t)node[k] / nx;
+        x[0] = (uint32_t)node[k] - yz * nx;
+        x[2] = yz / ny;
+        x[1] = yz - x[2] * ny;
+        for (uint32_t c = first[2][x[2]]; c < first[2][x[2] + 1]; ++c)
+            for (uint32_t b = first[1][x[1]]; b < first[1][x[1] + 1]; ++b)
+                for (uint32_t a = first[0][x[0]]; a < first[0][x[0] + 1]; ++a) {
+                    const On at[3] = {on[0][a], on[1][b], on[2][c]};
+                    f((size_t)at[0].tile +
+                          (size_t)p.ntile[0] * ((size_t)at[1].tile + (size_t)p.ntile[1] * (size_t)at[2].tile),
+                      at);
+                }
     };
     out.first.assign((size_t)p.blocks + 1, 0u);
-    each([&](size_t, const int64_t*, size_t b, const On*) { ++out.first[b + 1]; });
+    uint32_t x[3];
+    for (size_t k = 0; k < node.size(); ++k)
+        each(k, x, [&](size_t b, const On*) { ++out.first[b + 1]; });
     for (size_t b = 0; b < p.blocks; ++b) {
         if (out.first[b + 1] > (uint32_t)lim.links) return false;
         out.first[b + 1] += out.first[b];
     }
     out.link.resize(out.first[p.blocks]);
     std::vector<uint32_t> next(out.first.begin(), out.first.end() - 1);
-    each([&](size_t k, const int64_t* x, size_t b, const On* at) {
+    const int stride[3] = {1, p.region[0], p.region[0] * p.region[1]};
+    std::vector<int> delta((size_t)Q, 0);   // region index of a node less that of its source
+    for (int i = 0; i < Q; ++i)
+        for (int a = 0; a < 3; ++a) delta[i] += e[i][a] * stride[a];
+    for (size_t k = 0; k < node.size(); ++k) {
         const int i = dir[k], ib = opp[i];
-        const bool at_end = x[0] + 1 == n[0];
-        // region index of x_f - e_j; at the outlet that is a node of the same
-        // column unless (x_f, j) is a link, whose own slot is at the periodic
-        // neighbour (two links would share the column's)
-        auto source = [&](int j, bool link) {
-            int r = 0;
-            for (int a = 2; a >= 0; --a) {
-                int loc = at[a].loc - e[j][a];
-                if (a == 0 && outflow && at_end && e[j][0] == -1 && !link) loc = at[0].loc;
-                if ((p.wrap >> a) & 1u) loc = (loc + p.region[a]) % p.region[a];
-                r = r * p.region[a] + loc;
+        const bool ibar = ibar_link[k] != 0;
+        const int parts = (e[i][0] != 0) + (e[i][1] != 0) + (e[i][2] != 0);
+        each(k, x, [&](size_t b, const On* at) {
+            const bool at_end = x[0] + 1 == nx;
+            const int r = at[0].loc + at[1].loc * stride[1] + at[2].loc * stride[2];
+            // region index of x_f - e_j; at the outlet that is a node of the same
+            // column unless (x_f, j) is a link, whose own slot is at the periodic
+            // neighbour (two links would share the column's)
+            auto source = [&](int j, bool link) {
+                const bool column = outflow && at_end && e[j][0] == -1 && !link;
+                int s = column ? r - delta[j] - 1 : r - delta[j];
+                for (int a = column ? 1 : 0; a < 3; ++a)
+                    if ((p.wrap >> a) & 1u) {
+                        const int loc = at[a].loc - e[j][a];
+                        s += loc < 0 ? stride[a] * p.region[a]
+                                     : loc >= p.region[a] ? -stride[a] * p.region[a] : 0;
+                    }
+                return (uint32_t)s;
+            };
+            auto elem = [&](int j, uint32_t r) { return (uint32_t)(j - 1) * (uint32_t)lim.stride + r; };
+            const uint32_t edge = std::min(std::min(at[0].edge, at[1].edge), at[2].edge);
+            const uint32_t mine = at[0].mine & at[1].mine & at[2].mine;
+            int seam = 0;
+            if (pressure && !ibar) {
+                if (e[ib][0] == 1 && x[0] == 0) seam = 1;
+                if (e[ib][0] == -1 && at_end) seam = -1;
             }
-            return (uint32_t)r;
-        };
-        auto elem = [&](int j, uint32_t r) { return (uint32_t)(j - 1) * (uint32_t)lim.stride + r; };
-        uint32_t r = 0, edge = 31;
-        bool mine = true;
-        int parts = 0;
-        for (int a = 2; a >= 0; --a) {
-            r = r * (uint32_t)p.region[a] + (uint32_t)at[a].loc;
-            parts += e[i][a] != 0;
-            if ((p.wrap >> a) & 1u) continue;
-            edge = std::min(edge, (uint32_t)std::min(at[a].loc, p.region[a] - 1 - at[a].loc));
-            mine = mine && at[a].loc >= p.halo && at[a].loc < p.halo + p.tile[a] &&
-                   (int64_t)at[a].tile * p.tile[a] + at[a].loc - p.halo < n[a];
-        }
-        int seam = 0;
-        if (pressure && !ibar_link[k]) {
-            if (e[ib][0] == 1 && x[0] == 0) seam = 1;
-            if (e[ib][0] == -1 && at_end) seam = -1;
-        }
-        out.link[next[b]++] = TileLink{
-            edge | (uint32_t)mine << 5 | (uint32_t)(parts == 1) << 6 | (uint32_t)(e[i][0] + 1) << 7 |
-                (uint32_t)(seam + 1) << 9,
-            (uint32_t)k, elem(i, source(i, true)) | elem(ib, source(ib, ibar_link[k] != 0)) << 16,
-            elem(i, r) | elem(ib, r) << 16};
-    });
+            out.link[next[b]++] = TileLink{
+                edge | mine << 5 | (uint32_t)(parts == 1) << 6 | (uint32_t)(e[i][0] + 1) << 7 |
+                    (uint32_t)(seam + 1) << 9,
+                (uint32_t)k, elem(i, source(i, true)) | elem(ib, source(ib, ibar)) << 16,
+                elem(i, (uint32_t)r) | elem(ib, (uint32_t)r) << 16};
+        });
+    }
     return true;
 }
 
