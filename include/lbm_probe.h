@@ -1,15 +1,18 @@
 /*
- * lbm_probe.h -- measurement probes of the lattice Boltzmann engine (not part
- * of the method).  Each runs an access pattern of the step or adjoint kernels
- * without their arithmetic, or a plain copy, on caller-owned device memory,
- * and times it with HIP events on a private stream: they are the practical
- * ceilings the kernels of include/lbm.h are compared against.  Same return
- * codes as lbm.h; no solver handle is involved.
+ * lbm_probe.h -- probes of the lattice Boltzmann engine (not part of the
+ * method).  lbm_tile_plan reports how a handle steps; each of the others runs
+ * an access pattern of the step or adjoint kernels without their arithmetic, or
+ * a plain copy, on caller-owned device memory, and times it with HIP events on
+ * a private stream: they are the practical ceilings the kernels of
+ * include/lbm.h are compared against.  Same return codes as lbm.h; they involve
+ * no solver handle.
  */
 #ifndef LBM_PROBE_H
 #define LBM_PROBE_H
 
 #include <stdint.h>
+
+#include "lbm.h"
 
 #ifdef __cplusplus
 extern "C" {
@@ -80,6 +83,13 @@ int lbm_blocked_pull_pattern_copy(int lattice, int precision, int32_t block, voi
  * lbm_pull_pattern_copy. */
 int lbm_aa_pattern_copy(int lattice, int precision, void *buf_dev, int64_t nx, int64_t ny,
                         int64_t nz, int32_t reps, double *ms_even, double *ms_odd);
+
+/* How lbm_step for n >= 1 steps would start now: *steps time steps in its first
+ * launch (1: single steps), and, where that launch is on tiles, its *blocks and
+ * the most cut links of one block's region (else 0).  Any pointer may be NULL.
+ * Errors: EINVAL, ESTATE (no geometry). */
+int lbm_tile_plan(const lbm_t *h, int64_t n, int64_t *steps, int64_t *blocks,
+                  int64_t *region_links);
 
 #ifdef __cplusplus
 }

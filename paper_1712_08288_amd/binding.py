@@ -82,6 +82,7 @@ _adj_pattern = _sig("lbm_adjoint_pattern_copy", _i, [_i, _i, _p, _p, _p, _i64, _
 _aa_pattern = _sig("lbm_aa_pattern_copy", _i, [_i, _i, _p, _i64, _i64, _i64, _i32, _p, _p])
 _blocked_pattern = _sig("lbm_blocked_pull_pattern_copy", _i,
                         [_i, _i, _i32, _p, _p, _i64, _i64, _i64, _i32, _p])
+_tile_plan = _sig("lbm_tile_plan", _i, [_p, _i64, _p, _p, _p])
 _last_err = _sig("lbm_last_error", C.c_char_p, [_p])
 _destroy = _sig("lbm_destroy", _i, [_p])
 
@@ -99,7 +100,7 @@ EXPORTED = ["lbm_create", "lbm_set_scheme", "lbm_set_two_node", "lbm_set_wall_de
             "lbm_last_step_ms", "lbm_last_error", "lbm_destroy"]
 # measurement probes (include/lbm_probe.h)
 EXPORTED_PROBES = ["lbm_stream_copy", "lbm_pull_pattern_copy", "lbm_adjoint_pattern_copy",
-                   "lbm_aa_pattern_copy", "lbm_blocked_pull_pattern_copy"]
+                   "lbm_aa_pattern_copy", "lbm_blocked_pull_pattern_copy", "lbm_tile_plan"]
 
 LATTICES = {"D2Q9": 0, "D3Q19": 1, "D3Q15": 2}
 PRECISIONS = {"fp64": 0, "fp32": 1}
@@ -381,6 +382,14 @@ class Solver:
 
     def step(self, n=1):
         self._chk(_step(self._h, int(n)), "step")
+
+    def tile_plan(self, n):
+        """How step(n) would start now (lbm_tile_plan): the steps of its first
+        launch, and the blocks and the most cut links of a region of a launch
+        on tiles (0 where the launch is of one step)."""
+        out = [_i64(), _i64(), _i64()]
+        self._chk(_tile_plan(self._h, int(n), *(C.byref(v) for v in out)), "tile_plan")
+        return tuple(v.value for v in out)
 
     @property
     def time(self):

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/lbm.h"
+#include "../../include/lbm_probe.h"
 #include "engine.hpp"
 #include "geometry.hpp"
 #include "lattice.hpp"
@@ -382,6 +383,7 @@ int set_tiles(lbm_t* h, const int (*vel)[3], lbe::TileLinks& links) {
         if (lbe::tile_links(p, n, lim, e.Q, vel, e.lk_node_h, e.lk_dir_h, e.ibar_is_link,
                             e.xbc == LBM_X_PRESSURE, e.xbc == LBM_X_OUTFLOW, links)) {
             e.tiles = p;
+            e.tiles.links = links.most;
             break;
         }
     if (!e.tiles.halo) return LBM_OK;
@@ -1038,6 +1040,18 @@ int lbm_step(lbm_t* h, int64_t n) {
         HIPCHK(h, hipEventRecord(e.ev1, e.stream));
         e.timed_steps = n;        // resolved in lbm_last_step_ms
     }
+    return LBM_OK;
+}
+
+int lbm_tile_plan(const lbm_t* h, int64_t n, int64_t* steps, int64_t* blocks,
+                  int64_t* region_links) {
+    if (!h || n < 1) return LBM_EINVAL;
+    const Engine& e = h->e;
+    if (!e.has_geometry) return LBM_ESTATE;
+    const int64_t m = tile_steps(e, e.t, n, true);
+    if (steps) *steps = std::max<int64_t>(m, 1);
+    if (blocks) *blocks = m > 1 ? (int64_t)e.tiles.blocks : 0;
+    if (region_links) *region_links = m > 1 ? (int64_t)e.tiles.links : 0;
     return LBM_OK;
 }
 

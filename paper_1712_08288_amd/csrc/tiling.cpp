@@ -202,8 +202,10 @@ bool tile_links(const TilePlan& p, const int64_t (&n)[3], const TileLimits& lim,
     uint32_t x[3];
     for (size_t k = 0; k < node.size(); ++k)
         each(k, x, [&](size_t b, const On*) { ++out.first[b + 1]; });
+    out.most = 0;
     for (size_t b = 0; b < p.blocks; ++b) {
-        if (out.first[b + 1] > (uint32_t)lim.links) return false;
+        out.most = std::max(out.most, out.first[b + 1]);
+        if (out.most > (uint32_t)lim.links) return false;
         out.first[b + 1] += out.first[b];
     }
     out.link.resize(out.first[p.blocks]);

@@ -25,6 +25,7 @@ struct TilePlan {
     int tile[3] = {0, 0, 0}, region[3] = {0, 0, 0}, ntile[3] = {0, 0, 0};
     uint32_t wrap = 0;
     unsigned blocks = 0;
+    unsigned links = 0;     // most cut links of a region, once tile_links has found them
 };
 
 // A cut link (x_f, i) as a block meets it: the LDS elements of f_i and f_ibar
@@ -38,10 +39,12 @@ struct TileLink {
     uint32_t bits, index, pulled, post;
 };
 
-// The links of every region, region b's at [first[b], first[b + 1]).
+// The links of every region, region b's at [first[b], first[b + 1]), at most
+// `most` of them.
 struct TileLinks {
     std::vector<uint32_t> first;
     std::vector<TileLink> link;
+    uint32_t most = 0;
 };
 
 // The plans that are expected to be faster than single steps, best first.
