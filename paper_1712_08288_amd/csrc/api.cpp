@@ -406,6 +406,19 @@ int set_tiles(lbm_t* h, const int (*vel)[3], lbe::TileLinks& links) {
     return LBM_OK;
 }
 
+// Whether two steps, all that is left, go into one launch on tiles.  A plan for
+// more steps than two reads a halo made for those.  Measured, two single steps
+// and one launch (us): D2Q9 FP32 1800x1300 61.1 and 62.9, 3000x2500 177 and 188
+// (FP32 1100x700 26.6 and 23.1; FP64 2048^2 201 and 186), D3Q15 FP32 64x64x4
+// and 128x64x2 without links 7.2 and 8.7, 7.3 and 8.2 (with links, whose single
+// steps take longer, 10.3 and 10.1, 10.9 and 8.4; with x covered by the region
+// 7.5 and 7.1 at 4x64x64).
+bool tiles_for_two(const Engine& e) {
+    if (e.tiles.halo == 2) return true;
+    if (e.D == 3) return e.n_links > 0 || (e.tiles.wrap & 1u);
+    return e.elem == 8 || e.tiles.blocks <= 2000;
+}
+
 // How many of the next `left` steps from time t one launch on tiles may take
 // (0 or 1: the single step).  The objectives summed per block in node order
 // (mean u_x, pressure drop) and, with Eq. (211), the drag need the single step
@@ -419,7 +432,8 @@ int64_t tile_steps(const Engine& e, int64_t t, int64_t left, bool accumulate) {
     }
     // equal launches rather than full ones and a short rest
     const int64_t launches = (left + e.tiles.halo - 1) / e.tiles.halo;
-    return launches > 0 ? (left + launches - 1) / launches : 0;
+    const int64_t m = launches > 0 ? (left + launches - 1) / launches : 0;
+    return m == 2 && left == 2 && !tiles_for_two(e) ? 1 : m;
 }
 
 // m forward steps from time e.t in one launch on tiles, the state after step s

@@ -235,3 +235,27 @@ def test_graph_replay_without_tiles(monkeypatch, precision):
         sv.close()
     for k, (a, b) in enumerate(zip(*runs)):
         assert np.array_equal(a, b, equal_nan=True), k
+
+
+# (elements of 4 bytes, many blocks; thin domains without links that do not wrap)
+@pytest.mark.parametrize("make,precision,two", [
+    (lambda: G.random_cylinders(1800, 1300, 300, 4.0, 7.0, seed=5), "fp32", 1),
+    (lambda: G.random_cylinders(1800, 1300, 300, 4.0, 7.0, seed=5), "fp64", 2),
+    (lambda: G.random_cylinders(640, 400, 60, 4.0, 7.0, seed=5), "fp32", 2),
+    (lambda: G.empty("D3Q15", (64, 64, 4)), "fp32", 1),
+    (lambda: G.empty("D3Q15", (4, 64, 64)), "fp32", 2),
+    (lambda: scattered("D3Q15", (64, 64, 4), 0.02), "fp32", 2),
+    (lambda: G.random_spheres(16, 16, 16, 2, 2.0, 3.0, seed=5), "fp64", 2)])
+def test_calls_of_two_steps(make, precision, two):
+    """One launch or two single steps, whichever is faster: the same state."""
+    geom = make()
+    ends = []
+    for calls in ((2, 2, 2), (6,)):
+        sv = solver(geom, precision, {})
+        assert sv.tile_plan(2)[0] == two and sv.tile_plan(4)[0] > 1
+        sv.init_deviation(start(geom))
+        for n in calls:
+            sv.step(n)
+        ends.append(sv.distribution())
+        sv.close()
+    assert np.array_equal(*ends, equal_nan=True)
