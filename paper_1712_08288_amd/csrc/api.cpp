@@ -390,9 +390,9 @@ int set_tiles(lbm_t* h, const int (*vel)[3], lbe::TileLinks& links) {
     static_assert(sizeof(lbe::TileLink) == sizeof(uint4), "device layout");
     int rc;
     HIPCHK(h, lbe::tile_setup(e));
-    // one table: the links, then the offsets in whole entries
+    // one table: the links, then the offsets in whole entries (there is room)
     const size_t nl = links.link.size();
-    links.link.resize(nl + (links.first.size() + 3) / 4);
+    links.link.resize(nl + lbe::offset_entries(links));
     std::memcpy(links.link.data() + nl, links.first.data(), links.first.size() * 4);
     rc = upload(h, e.d_tile_link, reinterpret_cast<const uint4*>(links.link.data()),
                 links.link.size());

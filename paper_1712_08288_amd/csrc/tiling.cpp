@@ -2,6 +2,7 @@
 #include "tiling.hpp"
 
 #include <algorithm>
+#include <new>
 
 namespace lbe {
 
@@ -148,9 +149,13 @@ std::vector<TilePlan> tile_plans(const int64_t (&n)[3], const TileLimits& lim, i
     return best;
 }
 
-bool tile_links(const TilePlan& p, const int64_t (&n)[3], const TileLimits& lim, int Q,
-                const int (*e)[3], const std::vector<int64_t>& node, const std::vector<int8_t>& dir,
-                const std::vector<uint8_t>& ibar_link, bool pressure, bool outflow, TileLinks& out) {
+// (the offsets count links in 32 bits)
+constexpr uint32_t kMostLinks = 1u << 31;
+
+static bool place_links(const TilePlan& p, const int64_t (&n)[3], const TileLimits& lim, int Q,
+                        const int (*e)[3], const std::vector<int64_t>& node,
+                        const std::vector<int8_t>& dir, const std::vector<uint8_t>& ibar_link,
+                        bool pressure, bool outflow, TileLinks& out) {
     // per direction and coordinate, the tiles whose region's inside (all but
     // its outermost layer) holds it, with the place in the region, how far that
     // is from the region's edge and whether it is the tile's own: those of
@@ -205,9 +210,10 @@ bool tile_links(const TilePlan& p, const int64_t (&n)[3], const TileLimits& lim,
     out.most = 0;
     for (size_t b = 0; b < p.blocks; ++b) {
         out.most = std::max(out.most, out.first[b + 1]);
-        if (out.most > (uint32_t)lim.links) return false;
+        if (out.most > (uint32_t)lim.links || out.first[b] > kMostLinks) return false;
         out.first[b + 1] += out.first[b];
     }
+    out.link.reserve((size_t)out.first[p.blocks] + offset_entries(out));
     out.link.resize(out.first[p.blocks]);
     std::vector<uint32_t> next(out.first.begin(), out.first.end() - 1);
     const int stride[3] = {1, p.region[0], p.region[0] * p.region[1]};
@@ -251,6 +257,17 @@ bool tile_links(const TilePlan& p, const int64_t (&n)[3], const TileLimits& lim,
         });
     }
     return true;
+}
+
+bool tile_links(const TilePlan& p, const int64_t (&n)[3], const TileLimits& lim, int Q,
+                const int (*e)[3], const std::vector<int64_t>& node, const std::vector<int8_t>& dir,
+                const std::vector<uint8_t>& ibar_link, bool pressure, bool outflow, TileLinks& out) {
+    try {
+        return place_links(p, n, lim, Q, e, node, dir, ibar_link, pressure, outflow, out);
+    } catch (const std::bad_alloc&) {
+        out = TileLinks{};
+        return false;
+    }
 }
 
 }  // namespace lbe

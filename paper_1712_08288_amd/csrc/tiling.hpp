@@ -2,6 +2,7 @@
 // the tile size and the number of steps, in plain C++ (no HIP).
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -47,6 +48,9 @@ struct TileLinks {
     uint32_t most = 0;
 };
 
+// entries of `link` that the offsets would take
+inline std::size_t offset_entries(const TileLinks& t) { return (t.first.size() + 3) / 4; }
+
 // The plans that are expected to be faster than single steps, best first.
 // Q, D: lattice, elem: bytes of a population value.
 std::vector<TilePlan> tile_plans(const int64_t (&n)[3], const TileLimits& lim, int Q, int D, int elem);
@@ -55,8 +59,9 @@ std::vector<TilePlan> tile_plans(const int64_t (&n)[3], const TileLimits& lim, i
 // can hold.
 TilePlan tile_plan(const int64_t (&n)[3], const TileLimits& lim, const int (&tile)[3], int halo);
 
-// The links of the plan's regions; false when one has more than a block can
-// hold.  node, dir: the links in table order, e: the Q velocities, ibar_link:
+// The links of the plan's regions, with room behind them for the offsets
+// (offset_entries); false when one has more than a block can hold or there is
+// no memory for them.  node, dir: the links in table order, e: the Q velocities, ibar_link:
 // whether (x_f, ibar) is a link too; pressure: seam terms in x; outflow: the
 // zero-gradient outlet.
 bool tile_links(const TilePlan& p, const int64_t (&n)[3], const TileLimits& lim, int Q,
