@@ -1241,7 +1241,8 @@ int lbm_set_objective(lbm_t* h, int kind, int32_t tag, int64_t t_begin, int64_t 
     e.obj_tag = tag;
     e.obj_t0 = t_begin;
     e.obj_t1 = t_end;
-    const int64_t len = kind == LBM_OBJ_FORCE_X ? e.n_links + 1 : lbe::step_blocks(e);
+    // (the links' sums and the step count; an even number is cleared by one fill)
+    const int64_t len = kind == LBM_OBJ_FORCE_X ? (e.n_links + 2) / 2 * 2 : lbe::step_blocks(e);
     if (kind == LBM_OBJ_NONE || e.obj_acc_len != len) free_dev(e.d_obj_acc);
     e.obj_acc_len = 0;
     if (kind != LBM_OBJ_NONE) {
@@ -1296,7 +1297,7 @@ int lbm_objective(lbm_t* h, double* J) {
     *J = 0.0;
     if (e.obj_kind == LBM_OBJ_NONE || e.obj_acc_len == 0) return LBM_OK;
     const bool drag = e.obj_kind == LBM_OBJ_FORCE_X;
-    int rc = ensure_scratch(h, 4 + (drag ? 4 * lbe::link_blocks(e) : 0));
+    int rc = ensure_scratch(h, 4 + (drag ? 4 * lbe::drag_sum_blocks(e) : 0));
     if (rc) return rc;
     if (drag)
         HIPCHK(h, lbe::launch_drag_sums(e, e.d_obj_acc, e.obj_tag, e.d_scratch + 4, e.d_scratch));

@@ -250,8 +250,9 @@ hipError_t launch_force(Engine& e, const Snapshot& post, double* partials,
 hipError_t launch_force_objective(Engine& e, const Snapshot& post, double* acc,
                                   int tag, double weight);
 // out: the sum of acc in a fixed order, -e_ix summed over the tag's axis links
-// and over its diagonal links, the steps counted; partials: 4 link_blocks(e)
+// and over its diagonal links, the steps counted; partials: 4 drag_sum_blocks(e)
 // doubles
+int64_t drag_sum_blocks(const Engine& e);
 hipError_t launch_drag_sums(Engine& e, const double* acc, int tag, double* partials, double* out);
 // LBM_DEBUG: fill n values of T (the handle's precision) at p with NaN
 hipError_t launch_fill_nan(Engine& e, void* p, size_t n);
