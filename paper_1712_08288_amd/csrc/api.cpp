@@ -366,7 +366,8 @@ int forward_step(lbm_t* h, const Snapshot& in, const Snapshot& out, bool accumul
     }
     HIPCHK(h, lbe::launch_step(e, in, out, so, rec));
     if (in_window && e.obj_kind == LBM_OBJ_FORCE_X)
-        HIPCHK(h, lbe::launch_force_objective(e, out, e.d_obj_acc, e.obj_tag,
+        HIPCHK(h, lbe::launch_force_objective(e, out, e.d_obj_acc + lbe::kDragHeader,
+                                              e.obj_tag,
                                               1.0 / (double)(e.obj_t1 - e.obj_t0)));
     return LBM_OK;
 }
@@ -449,7 +450,7 @@ int forward_tiles(lbm_t* h, const Snapshot& in, const Snapshot* const* out, int6
         const int64_t s0 = std::max<int64_t>(e.obj_t0 - e.t, 0);
         const int64_t s1 = std::min<int64_t>(e.obj_t1 - e.t, m);
         if (s0 < s1) {
-            drag.acc = e.d_obj_acc;
+            drag.acc = e.d_obj_acc + lbe::kDragHeader;
             drag.tag = e.obj_tag;
             drag.s0 = (int)s0;
             drag.s1 = (int)s1;
@@ -1241,8 +1242,9 @@ int lbm_set_objective(lbm_t* h, int kind, int32_t tag, int64_t t_begin, int64_t 
     e.obj_tag = tag;
     e.obj_t0 = t_begin;
     e.obj_t1 = t_end;
-    // (the links' sums and the step count; an even number is cleared by one fill)
-    const int64_t len = kind == LBM_OBJ_FORCE_X ? (e.n_links + 2) / 2 * 2 : lbe::step_blocks(e);
+    // (the step count and the links' sums; an even number is cleared by one fill)
+    const int64_t len = kind == LBM_OBJ_FORCE_X ? lbe::kDragHeader + (e.n_links + 1) / 2 * 2
+                                                : lbe::step_blocks(e);
     if (kind == LBM_OBJ_NONE || e.obj_acc_len != len) free_dev(e.d_obj_acc);
     e.obj_acc_len = 0;
     if (kind != LBM_OBJ_NONE) {
@@ -1300,7 +1302,7 @@ int lbm_objective(lbm_t* h, double* J) {
     int rc = ensure_scratch(h, 4 + (drag ? 4 * lbe::drag_sum_blocks(e) : 0));
     if (rc) return rc;
     if (drag)
-        HIPCHK(h, lbe::launch_drag_sums(e, e.d_obj_acc, e.obj_tag, e.d_scratch + 4, e.d_scratch));
+        HIPCHK(h, lbe::launch_drag_sums(e, e.d_obj_acc + lbe::kDragHeader, e.obj_tag, e.d_scratch + 4, e.d_scratch));
     else
         HIPCHK(h, lbe::launch_sum_blocks(e, e.d_obj_acc, e.obj_acc_len, 1, e.d_scratch));
     double sum[4] = {0.0, 0.0, 0.0, 0.0};

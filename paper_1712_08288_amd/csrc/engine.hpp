@@ -124,7 +124,7 @@ struct Engine {
     int64_t obj_x_in = 0, obj_x_out = -1;   // pressure-drop planes (-1: nx - 1)
     double obj_a_in = 0.0, obj_a_out = 0.0; // 1 / (fluid nodes of each plane)
     std::vector<int64_t> fluid_per_x;       // fluid nodes of each plane x = const
-    double* d_obj_acc = nullptr;        // partial sums: per link and the steps (drag) or per block
+    double* d_obj_acc = nullptr;        // partial sums: the steps and per link (drag) or per block
     int64_t obj_acc_len = 0;
 
     // checkpointed run and adjoint
@@ -245,8 +245,16 @@ hipError_t launch_plane_density(Engine& e, const Snapshot& in, uint32_t x_in, ui
 // per-block partial momentum-exchange force: (nblocks, n_tags, D)
 hipError_t launch_force(Engine& e, const Snapshot& post, double* partials,
                         int64_t* nblocks);
+// Where the drag objective counts its steps, ahead of its links' sums acc.
+constexpr int kDragHeader = 2;          // in doubles: the sums stay on 16 bytes
+__host__ __device__ inline unsigned long long* step_count(double* acc) {
+    return reinterpret_cast<unsigned long long*>(acc) - kDragHeader;
+}
+__host__ __device__ inline const unsigned long long* step_count(const double* acc) {
+    return reinterpret_cast<const unsigned long long*>(acc) - kDragHeader;
+}
 // acc[k] += weight times the x force of link k's deviations, for the links of
-// one tag; the step is counted in acc[n_links] (a 64-bit integer)
+// one tag; the step is counted in step_count(acc)
 hipError_t launch_force_objective(Engine& e, const Snapshot& post, double* acc,
                                   int tag, double weight);
 // out: the sum of acc in a fixed order, -e_ix summed over the tag's axis links
@@ -280,9 +288,9 @@ TileLimits tile_limits(const Engine& e);
 // once per plan, with the handle's device current
 hipError_t tile_setup(const Engine& e);
 // drag of the launch's steps s0 <= s < s1: weight times the x force of link k's
-// deviations is added to acc[k] for the links of one tag and s1 - s0 to the
-// step count acc[n_links] (acc null: none; not with Eq. (211), whose link
-// values the last step does not complete)
+// deviations is added to acc[k] for the links of one tag and s1 - s0 to
+// step_count(acc) (acc null: none; not with Eq. (211), whose link values the
+// last step does not complete)
 struct TileDrag {
     double* acc = nullptr;
     int tag = 0, s0 = 0, s1 = 0;

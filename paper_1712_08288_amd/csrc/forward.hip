@@ -405,7 +405,7 @@ k_force(const T* __restrict__ B, const T* __restrict__ wa,
 }
 
 // The drag objective's sums: acc[k] collects weight times the x force of link
-// k's deviations, element n_links counts the steps (an integer).  The force's
+// k's deviations, step_count(acc) counts the steps.  The force's
 // constant part 2 w_i rho0 e_ix cancels between the links of a closed obstacle
 // and is added when the objective is read (k_drag_sums): collected with the
 // rest, its round-off was what the mean drag was short of (random cylinders
@@ -417,7 +417,7 @@ k_force_obj(const T* __restrict__ B, const T* __restrict__ wa,
             const int32_t* __restrict__ lktag, uint32_t n_links, Grid g, Params<L, T> p,
             int tag, double weight, double* __restrict__ acc) {
     const uint32_t k = blockIdx.x * BX + threadIdx.x;
-    if (k == 0) (void)atomicAdd(reinterpret_cast<unsigned long long*>(acc) + n_links, 1ull);
+    if (k == 0) (void)atomicAdd(step_count(acc), 1ull);
     double fx = 0;
     if (k < n_links && lktag[k] == tag) {
         const int i = lkdir[k];
@@ -464,8 +464,7 @@ k_drag_sums(const double* __restrict__ acc, const uint8_t* __restrict__ lkdir,
     if (threadIdx.x == 0) {
         double* row = partials + (size_t)blockIdx.x * 4;
         for (int c = 0; c < 3; ++c) row[c] = s[c];
-        row[3] = blockIdx.x ? 0.0
-                            : (double)reinterpret_cast<const unsigned long long*>(acc)[n_links];
+        row[3] = blockIdx.x ? 0.0 : (double)*step_count(acc);
     }
 }
 

@@ -64,7 +64,6 @@ struct TileArgs {
     // drag of the steps s with s0 <= s < s1 (TileDrag)
     double* acc;
     const int32_t* lktag;
-    uint32_t n_all;     // links of the domain: the step count's place in acc
     int tag, s0, s1;
     double weight;
     double ws[kTileSteps];   // factor on the wall terms of each step
@@ -124,9 +123,6 @@ k_tile_steps(const T* __restrict__ A, const T* __restrict__ waA, TileOut<T> out,
     // (1999x1501 FP64 5% and 1024x512 8% less time per step).
     const uint32_t block = (blockIdx.x & 7u) * a.per_xcd + (blockIdx.x >> 3);
     if (block >= a.blocks) return;
-    if (a.acc && block == 0 && t == 0)
-        (void)atomicAdd(reinterpret_cast<unsigned long long*>(a.acc) + a.n_all,   // not waited for
-                        (unsigned long long)(a.s1 - a.s0));
     const uint32_t l0 = a.first[block], n_links = a.first[block + 1] - l0;
     const bool has_link = (uint32_t)t < n_links, has_more = (uint32_t)(t + NT) < n_links;
     const uint4 lk = has_link ? a.link[l0 + (uint32_t)t] : uint4{0u, 0u, 0u, 0u};
@@ -183,8 +179,21 @@ k_tile_steps(const T* __restrict__ A, const T* __restrict__ waA, TileOut<T> out,
     auto drags = [&](const uint4& l) {
         return a.acc && ((l.x >> 5) & 1u) && ((l.x >> 7) & 3u) != 1u && a.lktag[l.y] == a.tag;
     };
-    const bool drag_own = has_link && drags(lk);
-    double drag = drag_own ? a.acc[lk.y] : 0.0;
+    // its weight, -e_ix times the window's: without a condition of the link's own
+    // left, the drag is one branch of the launch in a step (80x42 FP64 without
+    // drag 636 -> 632 us)
+    auto weight_of = [&](const uint4& l) { return a.weight * (1.0 - (double)((l.x >> 7) & 3u)); };
+    bool drag_own = false;
+    double drag = 0.0, drag_weight = 0.0;
+    unsigned long long counted = 0ull;   // by one thread: the steps before these
+    if (a.acc) {
+        drag_own = has_link && drags(lk);
+        if (drag_own) {
+            drag_weight = weight_of(lk);
+            drag = a.acc[lk.y];
+        }
+        if (block == 0 && t == 0) counted = *step_count(a.acc);
+    }
 #pragma unroll
     for (int m = 0; m < NPT; ++m)
         if (!is_solid(st[m]))
@@ -227,6 +236,9 @@ k_tile_steps(const T* __restrict__ A, const T* __restrict__ waA, TileOut<T> out,
     // all loads are back here; said outright, because else the compiler waits
     // for f in every step, and so for the coefficients each step loads ahead
     __builtin_amdgcn_s_waitcnt(0);
+    if (a.acc)
+        if (block == 0 && t == 0)
+            *step_count(a.acc) = counted + (unsigned long long)(a.s1 - a.s0);
     __syncthreads();
 
     for (int s = 0; s < a.steps; ++s) {
@@ -320,11 +332,12 @@ k_tile_steps(const T* __restrict__ A, const T* __restrict__ waA, TileOut<T> out,
         if (n_links) {
             __syncthreads();
             const double ws = wall_scale[s];
+            const bool in_window = s >= a.s0 && s < a.s1;
             T* __restrict__ waB = out_wa[s];
             // keeps the conversions to double, and with them the wait for the
             // coefficients, behind the barrier
             asm volatile("" : "+v"(lc.c1), "+v"(lc.c2), "+v"(lc.c3), "+v"(lc.wall));
-            auto update = [&](const uint4& l, T gi, T gib, const LinkCoefT<T>& c, bool in_drag,
+            auto update = [&](const uint4& l, T gi, T gib, const LinkCoefT<T>& c, double weight,
                               double& sum) {
                 const T fpi = F[l.w & 0xFFFFu], fpib = F[l.w >> 16];
                 const double v = p.c0 * (double)gi + c.c1 * (double)gib + c.c2 * (double)fpi +
@@ -337,18 +350,15 @@ k_tile_steps(const T* __restrict__ A, const T* __restrict__ waA, TileOut<T> out,
                     if (c1 != 0.0) next = (T)((double)next + c1 * (double)pulled_ibar(l));
                 }
                 F[l.z & 0xFFFFu] = next;
-                if (in_drag && s >= a.s0 && s < a.s1) {
-                    const int ex = (int)((l.x >> 7) & 3u) - 1;
-                    sum += a.weight * (-(double)ex * ((double)fpib + (double)next));
-                }
+                if (in_window) sum += weight * ((double)fpib + (double)next);
             };
-            if ((int)(lk.x & 31u) >= need) update(lk, fi, fib, lc, drag_own, drag);
+            if ((int)(lk.x & 31u) >= need) update(lk, fi, fib, lc, drag_weight, drag);
             if (has_more) {
                 const uint4 l = a.link[l0 + (uint32_t)(t + NT)];
                 if ((int)(l.x & 31u) >= need) {
                     const bool in_drag = drags(l);
                     double sum = in_drag ? a.acc[l.y] : 0.0;
-                    update(l, later[t], later[t + NT], lkcoef[l.y], in_drag, sum);
+                    update(l, later[t], later[t + NT], lkcoef[l.y], in_drag ? weight_of(l) : 0.0, sum);
                     if (in_drag) a.acc[l.y] = sum;
                 }
             }
@@ -415,7 +425,6 @@ hipError_t launch_tile_steps(Engine& e, const Snapshot& in, const Snapshot* cons
     a.steps = steps;
     a.acc = drag.acc;
     a.lktag = e.d_lktag;
-    a.n_all = (uint32_t)e.n_links;
     a.tag = drag.tag;
     a.s0 = drag.s0;
     a.s1 = drag.s1;
