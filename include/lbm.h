@@ -141,7 +141,9 @@ int lbm_set_x_boundary(lbm_t *h, int kind, double drho);
  * listed direction must have a solid pull source.  The coefficients of
  * Eq. (213) are computed here in double and checked against Eq. (212).
  * Errors: EINVAL (q, rule violates Eq. (212), more than 2^26 links),
- * EGEOM (inconsistent mask/links, fluid at x = 0 with OUTFLOW), ENOMEM. */
+ * EGEOM (inconsistent mask/links, fluid at x = 0 with OUTFLOW), ENOMEM.
+ * A violated Eq. (212) and ENOMEM leave the handle without a geometry (ESTATE
+ * from what needs one), the others leave the previous one. */
 int lbm_set_geometry(lbm_t *h, const uint8_t *solid, int64_t n_links,
                      const int64_t *node, const int8_t *dir, const double *q,
                      const double *wall_u, const int32_t *tag);

@@ -151,9 +151,9 @@ __device__ __forceinline__ void walk_links(const NodeLinks& nl, LinkStage<T>& st
 }
 
 // Sums over the lanes of a wave of N values each.  At every level the two
-// halves of the lanes exchange one half of the values each, so 24 exchanges
-// reduce 22 values where a reduction of one value after the other takes 132;
-// afterwards a lane holds one sum.
+// halves of the lanes exchange one half of the values each, so 17 exchanges
+// reduce the 15 rates of D3Q19 where a reduction of one value after the other
+// takes 90; afterwards a lane holds one sum.
 template <int N, int M>
 __device__ __forceinline__ void wave_sums(double* v, uint32_t lane) {
     if constexpr (N == 1) {

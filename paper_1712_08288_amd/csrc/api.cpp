@@ -610,10 +610,11 @@ int adjoint_steps(lbm_t* h, int64_t n) {
                 const int64_t nrep = j + 1 == nseg ? len : len - 1;
                 for (int64_t k = 0; k < nrep;) {
                     e.t = t_seg + k;   // the steps read e.t for the wall data
-                    // Tiles where a launch's length counts and every block runs at
-                    // once; storing each step's tile in turn is slower on larger
-                    // domains (2048x1024 FP64 88 us per step, single steps 53;
-                    // 512x256 3.4 and 7.0)
+                    // Tiles where a launch's length counts: the blocks run at
+                    // once, or in two turns where the CU holds one (FP64 in three
+                    // dimensions); storing each step's tile in turn is slower on
+                    // larger domains (2048x1024 FP64 88 us per step, single steps
+                    // 53; 512x256 3.4 and 7.0)
                     const int64_t m = e.tiles.blocks <= 512 ? tile_steps(e, e.t, nrep - k, false) : 0;
                     if (m > 1) {
                         const Snapshot* out[lbe::kTileSteps] = {};

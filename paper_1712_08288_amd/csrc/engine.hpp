@@ -19,8 +19,8 @@ constexpr int64_t kNoAllocScratchDoubles = 1 << 19;
 // reverse steps on records whose link gradient terms are added in one pass
 constexpr int kAkBatch = 8;
 
-// per cut link: the Eq. (213) coefficients, computed in double on the host
-// and stored in the precision of the populations (an FP32 handle combines
+// per cut link: the Eq. (213) coefficients, computed in double (links.hip) and
+// stored in the precision of the populations (an FP32 handle combines
 // them in double all the same)
 template <class T>
 struct LinkCoefT {

@@ -17,9 +17,9 @@
 // with three barriers, 0.6 to 0.9 us per step (small ones).  Single steps and
 // tiles, us per step: D2Q9 FP64 64x64 4.7 and 1.3, 1024x512 16.7 and 7.7,
 // 1999x1501 71 and 35; FP32 2048x2048 50.2 and 25.9; D3Q15 FP64 2x44x44 5.9
-// and 2.1.  A three-dimensional halo costs more than it saves on domains that
-// are not thin: 48^3 D3Q19 FP32 8.5 in single steps, 8.8 in tiles of 6^3 and
-// two steps.
+// and 2.1; 16^3 D3Q19 FP64 6.2 and 3.9.  On three-dimensional domains beyond
+// some 24^3 that are not thin the halo costs more than it saves: 48^3 D3Q19 FP32
+// 8.5 in single steps, 8.8 in tiles of 6^3 and two steps.
 //
 // In the LDS array a cut link (x_f, i) keeps its value f_i(x_f, t) in the slot
 // of direction i at its solid node x_f - e_i, which is where the pull of f_i

@@ -27,7 +27,8 @@ TilePlan tile_plan(const int64_t (&n)[3], const TileLimits& lim, const int (&til
 namespace {
 
 // Microseconds that a launch of plan p takes on 256 CUs, to compare plans by.
-// Fitted to D2Q9 launches of 2..12 steps on 64 x 64 to 2048 x 2048 nodes.
+// Fitted to D2Q9 launches of 2..12 steps on 64 x 64 to 2048 x 2048 nodes; in
+// three dimensions checked against measured launches only (see tile_plans).
 constexpr double kCus = 256, kBytesPerUs = 6.2e6, kLaunch = 3.0, kChain = 0.62;
 
 // In two parts, without and with the bytes moved: the first alone rules most
@@ -77,11 +78,15 @@ std::vector<TilePlan> tile_plans(const int64_t (&n)[3], const TileLimits& lim, i
     const double nodes = (double)n[0] * (double)n[1] * (double)n[2];
     const double single = std::max(4.0, 2.0 + 2.0 * Q * elem * nodes / kBytesPerUs);
     const double node = Q == 9 ? 1.0 : Q == 15 ? 1.9 : 2.5;
-    // Regions over 512 nodes in three dimensions lose more to the halo than a
-    // launch costs, so on domains that are not thin no plan passes the test
-    // against single steps below; it asks for a clear gain, because the figures
-    // compared are estimates (measured: the chosen plan within 6% of the best
-    // of those tried on 18 domains).
+    // A plan has to beat single steps clearly, because the figures compared are
+    // estimates (measured: the chosen plan within 6% of the best of those tried
+    // on 18 plane domains).  In three dimensions the halo soon costs more than
+    // it saves: cubes have plans up to 16^3 (D3Q19 FP64), 18^3 (D3Q15 FP64) and
+    // 24^3 (FP32), of 2 or 3 steps, and thin domains.  Measured against the 64
+    // steps of a replayed graph, us per step: 16^3 D3Q19 FP64 6.2 and 3.9, FP32
+    // 5.8 and 3.1; 24^3 D3Q19 FP32 7.4 and 4.1.  Of the sizes from 8^3 to 48^3
+    // and thin ones up to 128x64x2 and 2x88x88, D3Q15 and D3Q19 in both
+    // precisions, those with a plan took 0.27 to 0.83 of their single steps.
     double limit = 0.85 * single;
     static const int halos[] = {16, 12, 10, 8, 7, 6, 5, 4, 3, 2};
     static const int sizes[] = {2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 28, 32, 40, 48, 56, 64};
