@@ -440,10 +440,7 @@ k_adjoint(const T* __restrict__ A, StepRecord<T> rec, const T* __restrict__ wa,
             }
             // M (f - f^eq), so that f and its pairs die here
             T neq[Q];
-            if constexpr (WANT_DS) {
-                moments_of<L, T>(f[0], sp, dp, neq);
-                subtract_equilibrium<L, T>(neq, rho, j, p.inv_rho0);
-            }
+            if constexpr (WANT_DS) nonequilibrium_of<L, T>(f[0], sp, dp, j, p.inv_rho0, neq);
 
             // mu_i(y) = dJ/df'_i(y): lambda_i(y + e_i, t+1) where that node pulls
             T mu[Q];

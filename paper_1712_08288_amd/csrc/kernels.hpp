@@ -268,21 +268,28 @@ __device__ __forceinline__ void conserved_of(T x0, const T (&sp)[NPAIR<L>],
     else j[2] = T(0);
 }
 
-// m_k -= m^eq_k(drho, j) for the non-conserved rows (projection of Eq. (42))
+// M (f - f^eq) for the non-conserved rows: the residual rows (Residuals) and
+// the quadratic part of the projection of Eq. (42)
 template <class L, class T>
-__device__ __forceinline__ void subtract_equilibrium(T (&m)[L::Q], T rho, const T (&j)[3],
-                                                     T inv_rho0) {
+__device__ __forceinline__ void nonequilibrium_of(T x0, const T (&sp)[NPAIR<L>],
+                                                  const T (&dp)[NPAIR<L>], const T (&j)[3],
+                                                  T inv_rho0, T (&m)[L::Q]) {
     const T u[3] = {j[0] * inv_rho0, j[1] * inv_rho0, j[2] * inv_rho0};
     const T jj[6] = {j[0] * u[0], j[1] * u[1], j[2] * u[2],
                      j[0] * u[1], j[1] * u[2], j[0] * u[2]};
     unroll<L::Q>([&](auto K) {
         constexpr int k = decltype(K)::value;
+        m[k] = T(0);
         if constexpr (!L::conserved(k)) {
-            if constexpr (DER<L>.A[k] != 0.0) m[k] -= T(DER<L>.A[k]) * rho;
-            unroll<3>([&](auto X) {
-                constexpr int x = decltype(X)::value;
-                if constexpr (DER<L>.B[k][x] != 0.0) m[k] -= T(DER<L>.B[k][x]) * j[x];
+            Sum<T> acc;
+            unroll<FAC<L>.nclass>([&](auto C) {
+                constexpr int c = decltype(C)::value;
+                if constexpr (RES<L>.c[k][c] != 0.0)
+                    acc.term(T(RES<L>.c[k][c]),
+                             class_sum<L, FAC<L>.group[k], c, T>(DER<L>.even[k] ? sp : dp));
             });
+            if constexpr (RES<L>.c0[k] != 0.0) acc.term(T(RES<L>.c0[k]), x0);
+            m[k] = acc.v;
             unroll<6>([&](auto C) {
                 constexpr int c = decltype(C)::value;
                 if constexpr (DER<L>.C[k][c] != 0.0) m[k] -= T(DER<L>.C[k][c]) * jj[c];
@@ -354,8 +361,7 @@ __device__ __forceinline__ void collide(T (&f)[L::Q], const Params<L, T>& p,
     mac.u[1] = j[1] * p.inv_rho0;
     mac.u[2] = j[2] * p.inv_rho0;
     T r[L::Q];
-    moments_of<L, T>(f[0], sp, dp, r);
-    subtract_equilibrium<L, T>(r, rho, j, p.inv_rho0);
+    nonequilibrium_of<L, T>(f[0], sp, dp, j, p.inv_rho0, r);
     unroll<L::Q>([&](auto K) {
         constexpr int k = decltype(K)::value;
         if constexpr (KEEP_NEQ) neq[k] = r[k];

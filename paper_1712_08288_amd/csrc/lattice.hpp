@@ -175,23 +175,25 @@ struct Derived {
             even[k] = true;
             for (int i = 0; i < L::Q; ++i)
                 if (t.M[k][t.opp[i]] != t.M[k][i]) even[k] = false;
-            double a = 0, b[3] = {0, 0, 0}, c[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+            // sums over M_ki w_i in units of 1/72, which every weight is a
+            // multiple of: whole numbers, divided once
+            int a = 0, b[3] = {0, 0, 0}, c[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
             for (int i = 0; i < L::Q; ++i) {
-                const double mw = t.M[k][i] * L::W[i];
+                const int mw = t.M[k][i] * (int)(72.0 * L::W[i] + 0.5);
                 a += mw;
                 for (int x = 0; x < 3; ++x) {
-                    b[x] += 3.0 * mw * L::E[i][x];
-                    for (int y = 0; y < 3; ++y) c[x][y] += 4.5 * mw * L::E[i][x] * L::E[i][y];
+                    b[x] += mw * L::E[i][x];
+                    for (int y = 0; y < 3; ++y) c[x][y] += mw * L::E[i][x] * L::E[i][y];
                 }
             }
-            A[k] = a;
-            for (int x = 0; x < 3; ++x) B[k][x] = b[x];
-            C[k][0] = c[0][0] - 1.5 * a;
-            C[k][1] = c[1][1] - 1.5 * a;
-            C[k][2] = c[2][2] - 1.5 * a;
-            C[k][3] = 2.0 * c[0][1];
-            C[k][4] = 2.0 * c[1][2];
-            C[k][5] = 2.0 * c[0][2];
+            A[k] = a / 72.0;
+            for (int x = 0; x < 3; ++x) B[k][x] = 3 * b[x] / 72.0;
+            C[k][0] = (9 * c[0][0] - 3 * a) / 144.0;
+            C[k][1] = (9 * c[1][1] - 3 * a) / 144.0;
+            C[k][2] = (9 * c[2][2] - 3 * a) / 144.0;
+            C[k][3] = 9 * c[0][1] / 72.0;
+            C[k][4] = 9 * c[1][2] / 72.0;
+            C[k][5] = 9 * c[0][2] / 72.0;
         }
     }
 };
@@ -203,9 +205,11 @@ inline constexpr Derived<L> DER{};
 // are multiples of each other -- density, e and eps are constant there, j_x and
 // q_x are e_x, p_xx and pi_xx are 3 e_x^2 - |e|^2 -- so that a transform sums
 // each distinct pattern once per class and combines the sums, and back.  The
-// collision takes 199 floating-point instructions per D3Q19 node so, 245 with
-// every row summed on its own (D3Q15 152 and 175, D2Q9 78 and 85); a step on
-// tiles, bound by the issue of these, 27.4 -> 25.9 us at 2048x2048 FP32.
+// collision takes 192 floating-point instructions per D3Q19 node so (with the
+// residual rows below; 199 with the equilibrium subtracted), 245 with every row
+// summed on its own (D3Q15 145, 152 and 175, D2Q9 74, 78 and 85); a step on
+// tiles, bound by the issue of these, takes 25.2, 25.9 and 27.4 us at 2048x2048
+// FP32.
 // Rows whose entries are parallel in every class form a group; v holds the
 // group's pattern on the pairs (coprime within a class) and c the factor of
 // row and class, M[k][i] = c[k][class] v[group][pair].
@@ -289,6 +293,46 @@ constexpr bool factors_hold() {
 }
 static_assert(factors_hold<D2Q9>() && factors_hold<D3Q15>() && factors_hold<D3Q19>(),
               "every row is its group's pattern times its class factors");
+
+// The rows less the linear part of their equilibria, (M_k - A_k - B_k.e) f, so
+// that M (f - f^eq) is this and the quadratic part.  Formed row by row from
+// moments, rho and j that are each rounded first, what is left of two large
+// numbers is their round-off, always the same one in a uniform flow: momentum
+// drifted (D2Q9 FP64, flow along x, 200 steps: 1e-15 of it rms, 1e-17 so).
+// c0 belongs to the population at rest, c to row and class as in Factors.
+template <class L>
+struct Residuals {
+    double c0[L::Q], c[L::Q][3];
+    constexpr Residuals() : c0(), c() {
+        const int momentum[3] = {3, 5, 7};
+        for (int k = 0; k < L::Q; ++k) {
+            c0[k] = TAB<L>.M[k][0] - DER<L>.A[k];
+            for (int j = 0; j < FAC<L>.nclass; ++j) {
+                c[k][j] = FAC<L>.c[k][j] - DER<L>.A[k] * FAC<L>.c[0][j];
+                for (int x = 0; x < L::D; ++x)
+                    c[k][j] -= DER<L>.B[k][x] * FAC<L>.c[momentum[x]][j];
+            }
+        }
+    }
+};
+
+template <class L>
+inline constexpr Residuals<L> RES{};
+
+template <class L>
+constexpr bool residuals_hold() {
+    for (int k = 0; k < L::Q; ++k)
+        for (int p = 0; p < (L::Q - 1) / 2; ++p) {
+            const int* e = L::E[DER<L>.pi[p]];
+            double row = TAB<L>.M[k][DER<L>.pi[p]] - DER<L>.A[k];
+            for (int x = 0; x < 3; ++x) row -= DER<L>.B[k][x] * e[x];
+            const double d = RES<L>.c[k][FAC<L>.cls[p]] * FAC<L>.v[FAC<L>.group[k]][p] - row;
+            if (d > 1e-14 || d < -1e-14) return false;
+        }
+    return true;
+}
+static_assert(residuals_hold<D2Q9>() && residuals_hold<D3Q15>() && residuals_hold<D3Q19>(),
+              "the linear parts of the equilibria lie in the rows' groups");
 
 // every row is even or odd, and the conserved rows are density and momentum
 template <class L>
