@@ -15,9 +15,9 @@
 // collisions and the load of the region (large domains: two blocks per CU, one
 // loads while the other computes) or a chain of LDS and arithmetic latencies
 // with three barriers, 0.6 to 0.9 us per step (small ones).  Single steps and
-// tiles, us per step: D2Q9 FP64 64x64 4.7 and 1.3, 1024x512 16.7 and 7.7,
-// 1999x1501 71 and 35; FP32 2048x2048 50.2 and 25.9; D3Q15 FP64 2x44x44 5.9
-// and 2.1; 16^3 D3Q19 FP64 6.2 and 3.9.  On three-dimensional domains beyond
+// tiles, us per step: D2Q9 FP64 64x64 4.7 and 1.3, 1024x512 16.7 and 7.4,
+// 1999x1501 71 and 34; FP32 2048x2048 50.2 and 25.2; D3Q15 FP64 2x44x44 5.9
+// and 2.0; 16^3 D3Q19 FP64 6.2 and 3.9.  On three-dimensional domains beyond
 // some 24^3 that are not thin the halo costs more than it saves: 48^3 D3Q19 FP32
 // 8.5 in single steps, 8.8 in tiles of 6^3 and two steps.
 //
